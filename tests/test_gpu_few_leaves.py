@@ -1,0 +1,47 @@
+"""GPU tests of the forms that batches of few leaves take: a leaf's photons
+shared by several workgroups, and the one-channel last layer of a CNN."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2010_01775_amd import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _photons(seed, counts):
+    rng = synth.rng_for(seed)
+    n = int(sum(counts))
+    dirs = synth.to_f32_dirs(synth.unit_vectors(rng, n)) if n else np.zeros((0, 3), np.float32)
+    w = rng.integers(0, 2 ** 32, n, dtype=np.uint64).astype(np.uint32)
+    off = np.concatenate([[0], np.cumsum(counts)]).astype(np.uint32)
+    return dirs, w, off
+
+
+def _i32(a):
+    return torch.from_numpy(np.ascontiguousarray(a).view(np.int32)).to(DEV)
+
+
+# counts about the slice size (2048) and its multiples; 512 leaf bands are the
+# last batch cut into slices; 256x256 maps have four bands
+@pytest.mark.parametrize("counts,H,W", [([0, 1, 2047, 2048, 4095, 4096, 4097, 200001], 32, 32),
+                                        ([70000], 4, 8), ([131073], 128, 128), ([50000, 3, 9000], 256, 256),
+                                        ([4100] * 512, 16, 16), ([4100] * 513, 16, 16)])
+def test_splat_slices_exact(ctx, npg, orc, counts, H, W):
+    dirs, w, off = _photons(len(counts) * H, counts)
+    perm = np.random.default_rng(1).permutation(len(w)).astype(np.uint32)
+    rc, e_ref, c_ref = orc.splat(dirs, w, off, H, W, perm=perm)
+    assert rc == 0
+    d, ww, o, p = torch.from_numpy(dirs).to(DEV), _i32(w), _i32(off), _i32(perm)
+    e = torch.full((len(counts), H, W), -1, dtype=torch.int64, device=DEV)
+    c = torch.full((len(counts), H, W), -1, dtype=torch.int32, device=DEV)
+    npg.splat_histograms(ctx, d, ww, o, H, W, perm=p, energy=e, count=c)
+    assert npg.sync_status(ctx) == 0
+    assert np.array_equal(e.cpu().numpy().view(np.uint64), e_ref)
+    assert np.array_equal(c.cpu().numpy().view(np.uint32), c_ref)
+    npg.splat_histograms(ctx, d, ww, o, H, W, perm=p, energy=e, count=c, accumulate=True)
+    npg.splat_histograms(ctx, d, ww, o, H, W, perm=p, energy=e, want_count=False, accumulate=True)
+    assert npg.sync_status(ctx) == 0
+    assert np.array_equal(e.cpu().numpy().view(np.uint64), e_ref * np.uint64(3))
+    assert np.array_equal(c.cpu().numpy().view(np.uint32), c_ref * np.uint32(2))
