@@ -584,6 +584,64 @@ __global__ __launch_bounds__(256) void head_kernel(const T *__restrict__ in, con
   out[pix] = (float)softplus_f(acc);
 }
 
+// A 3x3 convolution to one channel + softplus (the last layer of a CNN) on a
+// plain channel-last input of Cin = 16 n channels, binary64 sums.  One output
+// channel leaves the matrix cores nothing to tile, and the direct convolution
+// walks its 9 Cin inputs one dependent load at a time: 74 us for one 32x32
+// leaf of 16 channels, on 4 workgroups.  Here a workgroup owns a tile of TR x
+// TW <= 64 pixels with four lanes per pixel, each summing four channels of
+// every 16-channel chunk from the patch staged in LDS (all its loads in
+// flight at once), and the four sums meet in two shuffles: 16 workgroups for
+// that leaf, whose splat, network and tables together went from 104 to 46 us.
+// Small tiles rather than wide ones because the layer is bound by latency on
+// few leaves and by HBM reads on many, where the halo comes out of the L2.
+template <class T>
+__global__ __launch_bounds__(256) void conv_one_kernel(const T *__restrict__ in, float dq,
+                                                       const float *__restrict__ w, const float *__restrict__ b,
+                                                       int Cin, int H, int W, int TW, int TR,
+                                                       float *__restrict__ out) {
+  constexpr int G = sizeof(T);  // 16-byte pieces of a pixel's 16 channels
+  __shared__ uint4 patch[108 * G];  // (TR + 2) (TW + 2) <= 108 pixels (16 x 4)
+  const int tiles_x = W / TW, tpl = (H / TR) * tiles_x;
+  const int leaf = blockIdx.x / tpl, t = blockIdx.x - leaf * tpl;
+  const int ty0 = (t / tiles_x) * TR, tx0 = (t % tiles_x) * TW;
+  const int PW = TW + 2, np = (TR + 2) * PW;
+  const int pix = threadIdx.x >> 2, q = threadIdx.x & 3;
+  const bool act = pix < TR * TW;
+  const int ry = act ? pix / TW : 0, rx = act ? pix - ry * TW : 0;
+  const size_t base = (size_t)leaf * H * W;
+  double acc = 0.0;
+  for (int c0 = 0; c0 < Cin; c0 += 16) {
+    float wk[36];  // this lane's four channels, nine taps each
+    const float4 *w4 = reinterpret_cast<const float4 *>(w + (size_t)(c0 + 4 * q) * 9);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) reinterpret_cast<float4 *>(wk)[k] = w4[k];
+    if (c0) __syncthreads();
+    for (int i = threadIdx.x; i < np * G; i += 256) {
+      const int p = i / G, g = i - p * G;
+      const int y = ty0 - 1 + p / PW, x = tx0 - 1 + p % PW;
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (y >= 0 && y < H && x >= 0 && x < W)
+        v = reinterpret_cast<const uint4 *>(in + (base + (size_t)y * W + x) * Cin + c0)[g];
+      patch[i] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      T v[4];
+      __builtin_memcpy(v, reinterpret_cast<const T *>(patch) + ((ry + k / 3) * PW + rx + k % 3) * 16 + 4 * q, sizeof(v));
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const double x = sizeof(T) == 1 ? to_d<T>(v[c]) * (double)dq : to_d<T>(v[c]);
+        acc = fma((double)wk[c * 9 + k], x, acc);
+      }
+    }
+  }
+  acc += __shfl_xor(acc, 1);
+  acc += __shfl_xor(acc, 2);
+  if (act && q == 0) out[base + (size_t)(ty0 + ry) * W + tx0 + rx] = (float)softplus_f(acc + (double)b[0]);
+}
+
 // Sums of the four maps of the five-channel input per leaf (exact integer
 // sums, stored as binary64): tot[L][4] = (E_t, E_t-1, P_t, P_t-1).
 __global__ __launch_bounds__(256) void leaf_totals5_kernel(const uint64_t *__restrict__ e_t,
@@ -2033,6 +2091,27 @@ struct Runner {
       }
     }
     const size_t npix = (size_t)Lc * H * W;
+    // the last layer of a CNN, on whole chunks of 16 channels (its 16-byte
+    // loads); other channel counts take the direct convolution
+    if (!force_direct && act == ACT_SOFTPLUS && y.k == 3 && y.cout == 1 && y.dil == 1 && y.cin % 16 == 0 &&
+        src.mode == SRC_PLAIN && !res && !head) {
+      ctx->conv_flops[1] += 2.0 * npix * y.cin * 9;
+      const int TW = std::min(W, 8), TR = std::min(H, 64 / TW);
+      const size_t blocks = (size_t)Lc * (H / TR) * (W / TW);
+      if (blocks > 0x7fffffffu) return npg_fail(ctx, NPG_E_ARG, "internal: %zu tiles in one launch", blocks);
+      auto go = [&](auto tag) {
+        using TT = decltype(tag);
+        hipLaunchKernelGGL((conv_one_kernel<TT>), dim3((unsigned)blocks), dim3(256), 0, s,
+                           static_cast<const TT *>(src.s0), src.dq0, y.w, y.b, y.cin, H, W, TW, TR,
+                           static_cast<float *>(out));
+      };
+      if (prec == NPG_FP32) go(double{});
+      else if (prec == NPG_FP8) go(uint8_t{});
+      else go(uint16_t{});
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return npg_fail(ctx, NPG_E_HIP, "last conv launch: %s", hipGetErrorString(e));
+      return NPG_OK;
+    }
     // an unfused 1x1 head on 16 or 32 channels (FP32 or BF16 activations)
     if (!force_direct && act == ACT_SOFTPLUS && y.k == 1 && y.cout == 1 && src.mode == SRC_PLAIN && !res &&
         !head && prec != NPG_FP8 && (y.cin == 16 || y.cin == 32)) {

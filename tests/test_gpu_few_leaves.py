@@ -45,3 +45,22 @@ def test_splat_slices_exact(ctx, npg, orc, counts, H, W):
     assert npg.sync_status(ctx) == 0
     assert np.array_equal(e.cpu().numpy().view(np.uint64), e_ref * np.uint64(3))
     assert np.array_equal(c.cpu().numpy().view(np.uint32), c_ref * np.uint32(2))
+
+
+# maps narrower and wider than the 8x8 tile, one to three 16-channel chunks;
+# two layers leave the 1-channel layer's input stored
+@pytest.mark.parametrize("H,W,L,channels", [(4, 64, 2, (1, 16, 1)), (64, 4, 1, (1, 16, 1)), (16, 16, 3, (1, 48, 1)),
+                                            (8, 8, 5, (1, 32, 1)), (32, 64, 2, (1, 16, 16, 1))])
+def test_last_layer_one_channel(ctx, npg, orc, H, W, L, channels):
+    model = synth.cnn_model(H + W, channels=channels, random_bias=True)
+    dirs, w, off = _photons(H * W + L, [700 * (k + 1) for k in range(L)])
+    rc, e, _ = orc.splat(dirs, w, off, H, W)
+    assert rc == 0
+    rc, s_ref = orc.net_forward(model, orc.normalize_input(e))
+    assert rc == 0
+    m = npg.Model(ctx, model)
+    s = npg.reconstruct_density(ctx, m, torch.from_numpy(e.view(np.int64)).to(DEV), "fp32").cpu().numpy()
+    assert npg.sync_status(ctx) == 0
+    # binary64 sums on both sides: the float32 output's rounding, twice
+    assert np.max(np.abs(s - s_ref) / s_ref) < 2.0 ** -22
+    m.free()
