@@ -64,3 +64,46 @@ def test_last_layer_one_channel(ctx, npg, orc, H, W, L, channels):
     # binary64 sums on both sides: the float32 output's rounding, twice
     assert np.max(np.abs(s - s_ref) / s_ref) < 2.0 ** -22
     m.free()
+
+
+# rows of 1 to 64 lanes, one, four and eight pieces per thread, the last map
+# held in registers (32,768 bins) and the first past it; rows past 256 columns
+@pytest.mark.parametrize("H,W", [(4, 4), (4, 8), (16, 16), (64, 4), (8, 128), (32, 32), (32, 64), (64, 64), (128, 32),
+                                 (128, 128), (256, 128), (128, 256), (256, 256), (8, 512), (1024, 4)])
+def test_cdf_tables_every_form(ctx, npg, orc, H, W):
+    s = synth.random_density(H * 7 + W, 5, H, W, zero_frac=0.3)
+    s[1, H // 2] = 0.0  # a row without mass
+    s[2] = 0.0
+    s[2, H - 1, W - 1] = 1e-30  # all mass in the last bin
+    s[3] = np.float32(3e38)  # a sum past the float32 range
+    s[4, :, 0] = 1e-45  # float32's lowest value beside ordinary ones
+    pdf, marg, cond, tot = orc.build_cdf(s)[1:5]
+    t = npg.build_cdf(ctx, torch.from_numpy(s).to(DEV))
+    assert npg.sync_status(ctx) == 0
+    # one float32 rounding of binary64 values within a few roundings of each other
+    for got, ref in ((t.pdf, pdf), (t.marg, marg), (t.cond, cond)):
+        assert np.max(np.abs(got.cpu().numpy() - ref) / np.maximum(ref, 1e-30)) < 2.0 ** -22
+    assert np.max(np.abs(t.total.cpu().numpy() - tot) / tot) < 1e-13
+    m, c = t.marg.cpu().numpy(), t.cond.cpu().numpy()
+    assert np.all(np.diff(m, axis=1) >= 0) and np.all(np.diff(c, axis=2) >= 0)
+    assert np.all(m[:, 0] == 0) and np.all(m[:, -1] == 1) and np.all(c[..., 0] == 0) and np.all(c[..., -1] == 1)
+    # unaligned caller buffers give the same tables; a bad leaf only its own
+    def odd(x, fill):
+        b = torch.full((x.numel() + 1,), fill, dtype=x.dtype, device=DEV)
+        return b[1:].view(x.shape)
+    o = npg.CdfTables(odd(t.pdf, 7.0), odd(t.marg, 7.0), odd(t.cond, 7.0), t.total.clone())
+    s2 = odd(t.pdf, 0.0)
+    s2.copy_(torch.from_numpy(s))
+    npg.build_cdf(ctx, s2, out=o)
+    assert npg.sync_status(ctx) == 0
+    assert torch.equal(o.pdf, t.pdf) and torch.equal(o.marg, t.marg) and torch.equal(o.cond, t.cond)
+    for k, v in ((0, float("nan")), (2, -1.0), (4, float("inf"))):
+        s2[k, H - 1, W - 1] = v
+    npg.build_cdf(ctx, s2, out=o)
+    assert npg.sync_status(ctx) == npg.E_RANGE
+    for k in range(5):
+        if k in (0, 2, 4):
+            assert torch.isnan(o.pdf[k]).all() and torch.isnan(o.cond[k]).all() and torch.isnan(o.marg[k]).all()
+            assert o.total[k] == 0
+        else:
+            assert torch.equal(o.pdf[k], t.pdf[k]) and torch.equal(o.cond[k], t.cond[k])
