@@ -40,12 +40,8 @@
 #include <mutex>
 #include <vector>
 
+#include "conv_tile.h"
 #include "npg_internal.h"
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef long fp8x8;  // eight e4m3 bytes
 
 // ------------------------------------------------------------------ model
 struct LayerDev {
@@ -94,60 +90,7 @@ uint16_t f32_to_bf16_host(float f) {
   return (uint16_t)(u >> 16);
 }
 
-constexpr int KC32 = 16;  // input channels per chunk, FP32 path
-constexpr int KC16 = 32;  // input channels per chunk, BF16 path
-constexpr int KC16S = 16; // BF16 path for 16- and 48-channel inputs: one 32-wide
-                          // MFMA K slice covers two taps of 16 channels
-constexpr int KC8 = 32;   // FP8 path, as BF16
-constexpr int KC8S = 16;
-constexpr float E4M3_MAX = 448.0f;
-
 }  // namespace
-
-// OCP FP8 e4m3: 1 sign, 4 exponent bits (bias 7), 3 mantissa bits, no
-// infinities, 0x7f / 0xff NaN, largest finite 448, subnormal step 2^-9.
-// Encoding rounds to nearest even and saturates at +-448.
-__host__ __device__ inline uint8_t e4m3_enc(float x) {
-  if (x != x) return 0x7f;
-  uint8_t s = 0;
-  if (x < 0.0f) {
-    s = 0x80;
-    x = -x;
-  }
-  if (x >= E4M3_MAX) return s | 0x7e;
-  if (x < 0.015625f) return s | (uint8_t)rintf(x * 512.0f);  // subnormal (8 -> 0x08, the smallest normal)
-  int e;
-  (void)frexpf(x, &e);                          // x in [2^(e-1), 2^e)
-  int m = (int)rintf(ldexpf(x, 4 - e)) - 8;     // mantissa steps of 2^(e-4), in [0, 8]
-  int E = e - 1 + 7;
-  if (m == 8) {
-    m = 0;
-    ++E;
-  }
-  return s | (uint8_t)((E << 3) | m);  // x < 448 keeps (E, m) <= (15, 6)
-}
-__host__ __device__ inline float e4m3_dec(uint8_t v) {
-  const int e = (v >> 3) & 15, m = v & 7;
-  float mag = e ? ldexpf((float)(8 + m), e - 10) : ldexpf((float)m, -9);
-  if ((v & 0x7f) == 0x7f) mag = NAN;
-  return (v & 0x80) ? -mag : mag;
-}
-
-// Device forms on the conversion instructions (gfx950 converts to OCP e4m3
-// with round to nearest even; out-of-range inputs, which would give NaN,
-// are clamped first so that both forms saturate alike).
-__device__ __forceinline__ uint8_t e4m3_enc_d(float x) {
-  const float c = x != x ? x : fminf(fmaxf(x, -E4M3_MAX), E4M3_MAX);
-  return (uint8_t)(__builtin_amdgcn_cvt_pk_fp8_f32(c, c, 0, false) & 0xff);
-}
-__device__ __forceinline__ float e4m3_dec_d(uint8_t v) { return __builtin_amdgcn_cvt_f32_fp8((int)v, 0); }
-// Four values as four e4m3 bytes (first value in the low byte), each clamped
-// and rounded as e4m3_enc_d does: two conversion instructions.
-__device__ __forceinline__ float e4m3_clamp_d(float x) { return x != x ? x : fminf(fmaxf(x, -E4M3_MAX), E4M3_MAX); }
-__device__ __forceinline__ uint32_t e4m3_pack4_d(float a, float b, float c, float d) {
-  const int lo = __builtin_amdgcn_cvt_pk_fp8_f32(e4m3_clamp_d(a), e4m3_clamp_d(b), 0, false);
-  return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(e4m3_clamp_d(c), e4m3_clamp_d(d), lo, true);
-}
 
 // Parses the NPGW v1 file and checks the declared topology.
 static int parse_model(npg_ctx *ctx, const unsigned char *buf, size_t len, npg_model *m) {
@@ -363,40 +306,6 @@ extern "C" void npg_model_free(npg_model *m) {
 namespace {
 
 enum SrcMode : int { SRC_PLAIN = 0, SRC_POOL = 1, SRC_UPCAT = 2, SRC_ENERGY = 3, SRC_FIVE = 4 };
-enum Act : int { ACT_RELU = 0, ACT_SOFTPLUS = 1, ACT_ELU = 2 };
-
-// ReLU, or ELU (Clevert et al. 2016: x for x > 0, e^x - 1 otherwise).
-template <class A>
-__device__ __forceinline__ A act_fn(A v, int act) {
-  if (act == ACT_ELU) {
-    if constexpr (sizeof(A) == 8)
-      return v > (A)0 ? v : (A)expm1((double)v);
-    else
-      return v > (A)0 ? v : (A)expm1f((float)v);
-  }
-  return v > (A)0 ? v : (A)0;
-}
-
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
-// float -> bf16 bits, round to nearest even (one conversion instruction)
-__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
-
-__device__ __forceinline__ float softplus_f(float x) { return fmaxf(x, 0.0f) + log1pf(expf(-fabsf(x))); }
-__device__ __forceinline__ double softplus_f(double x) { return fmax(x, 0.0) + log1p(exp(-fabs(x))); }
-
-// activation storage types: double (FP32 mode) and bf16 bits (BF16 mode)
-template <class T> __device__ __forceinline__ double to_d(T v);
-template <> __device__ __forceinline__ double to_d<double>(double v) { return v; }
-template <> __device__ __forceinline__ double to_d<float>(float v) { return v; }
-template <> __device__ __forceinline__ double to_d<uint16_t>(uint16_t v) { return bf2f(v); }
-template <> __device__ __forceinline__ double to_d<uint8_t>(uint8_t v) { return e4m3_dec_d(v); }
-template <class T> __device__ __forceinline__ T from_d(double v);
-template <> __device__ __forceinline__ double from_d<double>(double v) { return v; }
-template <> __device__ __forceinline__ float from_d<float>(double v) { return (float)v; }
-template <> __device__ __forceinline__ uint16_t from_d<uint16_t>(double v) { return f2bf((float)v); }
-template <> __device__ __forceinline__ uint8_t from_d<uint8_t>(double v) { return e4m3_enc_d((float)v); }
-
 // Source tensors of one convolution's (virtual) input.
 struct Src {
   int mode;
@@ -912,8 +821,6 @@ struct ChunkSrc {
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0));
   }
 };
-// Buffer-resource word 3 for raw (unswizzled, untyped) buffers on gfx9.
-constexpr int BUF_WORD3 = 0x00020000;
 
 template <class T>
 __device__ __forceinline__ ChunkSrc<T> chunk_src(const ConvArgs &a, int leaf0, int c0) {
@@ -949,8 +856,6 @@ __device__ __forceinline__ ChunkSrc<T> chunk_src(const ConvArgs &a, int leaf0, i
 // and slots past nslots, write zeros).  The region is a whole number of
 // 1 KiB blocks.  No registers hold the data, so every load of a chunk is in
 // flight at once; the caller waits on vmcnt and a barrier before reading.
-typedef __attribute__((address_space(3))) void lds_void;
-constexpr size_t DMA_BLOCK = 1024;
 template <class F>
 __device__ __forceinline__ void dma_slots(__amdgpu_buffer_rsrc_t rs, char *lds, int nslots, int wave, int lane, F off) {
   const int ninst = (nslots + 63) >> 6;
@@ -1461,54 +1366,6 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvArgs a) {
     // 8/16-bit tiles hold the transposed product (weights as the A operand):
     // lane (lr, lg) has channels 16 ni + 4 lg + r, r = 0..3, of pixel
     // 16 mi + lr of its wavefront's block
-    if (a.head_w) {
-      float *dl = reinterpret_cast<float *>(smem);  // [BM] densities
-      AS bn[4], hw[4], ws[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        bn[r] = (AS)a.bias[4 * lg + r];
-        hw[r] = (AS)a.head_w[4 * lg + r];
-        ws[r] = (AS)1;
-        if constexpr (P::Q8) ws[r] = (AS)a.wsc[4 * lg + r];
-      }
-      AS mine = 0;
-#pragma unroll
-      for (int mi = 0; mi < MW; ++mi) {
-        AS v = 0;
-        // the values the unfused path would store (type T) feed the head
-        if constexpr (P::Q8) {
-          float q[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const AS v0 = acc[mi][0][r] * ws[r] + bn[r];
-            q[r] = (v0 > (AS)0 ? v0 : (AS)0) * a.oinv;
-          }
-          const int pk = (int)e4m3_pack4_d(q[0], q[1], q[2], q[3]);
-          const auto d01 = __builtin_amdgcn_cvt_pk_f32_fp8(pk, false), d23 = __builtin_amdgcn_cvt_pk_f32_fp8(pk, true);
-          const float dq[4] = {d01[0], d01[1], d23[0], d23[1]};
-#pragma unroll
-          for (int r = 0; r < 4; ++r) v += (AS)(dq[r] * a.asc) * hw[r];
-        } else {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const AS v0 = acc[mi][0][r] + bn[r];
-            v += (AS)bf2f(f2bf(v0 > (AS)0 ? v0 : (AS)0)) * hw[r];
-          }
-        }
-        v += __shfl_xor(v, 16);
-        v += __shfl_xor(v, 32);
-        if (lg == mi) mine = v;
-      }
-      if (lg < MW) dl[wave * 16 * MW + lg * 16 + lr] = (float)softplus_f(mine + (AS)a.head_b);
-      __syncthreads();
-      // four consecutive tile pixels are contiguous in the output (TW >= 4)
-      for (int i = tid; i < BM / 4; i += 256) {
-        const long g = gpix(i * 4);
-        if (g >= 0)
-          *reinterpret_cast<float4 *>(static_cast<float *>(a.out) + g) = *reinterpret_cast<const float4 *>(dl + i * 4);
-      }
-      return;
-    }
     // [BM][OP]: the row padding puts the 16 lanes of a group, which hold
     // 16 pixels of the same channels, in different LDS banks
     constexpr int OP = BN + 16 / (int)sizeof(T);
@@ -1730,13 +1587,18 @@ hipError_t launch_mfma_kx(const ConvArgs &a, size_t lds, unsigned tiles, hipStre
 
 template <class P, int MW, int NW, int MODE>
 hipError_t launch_mfma_k(const ConvArgs &a, size_t lds, unsigned tiles, hipStream_t s) {
-  // the extended form only for the layers that need it (8/16-bit and FP64
-  // tiles on plain, concatenated or pooled inputs; never FP8)
-  if (a.dil != 1 || a.act != ACT_RELU || a.res) {
-    if constexpr (MODE != 2 && !P::Q8) return launch_mfma_kx<P, MW, NW, MODE, true>(a, lds, tiles, s);
+  // the extended form only for the layers that need it (BF16 and FP64 tiles
+  // on plain, concatenated or pooled inputs), and for the 8/16-bit layers on
+  // plain or concatenated inputs that conv_tile_kernel has no tile for (maps
+  // of one or two rows), whose plain form is not compiled
+  const bool ext = a.dil != 1 || a.act != ACT_RELU || a.res;
+  if (ext || (!P::F64 && MODE == 0)) {
+    if (P::Q8 && ext) return hipErrorInvalidValue;
+    if constexpr (MODE != 2 && (!P::Q8 || MODE == 0)) return launch_mfma_kx<P, MW, NW, MODE, true>(a, lds, tiles, s);
     return hipErrorInvalidValue;
   }
-  return launch_mfma_kx<P, MW, NW, MODE, false>(a, lds, tiles, s);
+  if constexpr (P::F64 || MODE == 1) return launch_mfma_kx<P, MW, NW, MODE, false>(a, lds, tiles, s);
+  return hipErrorInvalidValue;
 }
 
 template <class P, int MW, int NW>
@@ -1747,7 +1609,7 @@ hipError_t launch_mfma_t(const ConvArgs &a, size_t lds, unsigned tiles, hipStrea
     return hipErrorInvalidValue;
   }
   if (a.src.mode == SRC_ENERGY) {
-    if constexpr (NW == 1 && P::KC <= 16 && 16 % P::KC == 0) return launch_mfma_k<P, MW, NW, 2>(a, lds, tiles, s);
+    if constexpr (P::F64 && NW == 1) return launch_mfma_k<P, MW, NW, 2>(a, lds, tiles, s);
     return hipErrorInvalidValue;
   }
   return launch_mfma_k<P, MW, NW, 0>(a, lds, tiles, s);
@@ -1821,6 +1683,46 @@ struct Runner {
     if (y.cin % KC16 == 0) return pick_tiling<BF16P>(y.cout, H, W, t, c, y.dil);
     return pick_tiling<BF16S>(y.cout, H, W, t, c, y.dil);
   }
+  // 8/16-bit layers on plain or concatenated inputs, whole 3x3 taps one pixel
+  // apart: the tiles with compile-time geometry (conv_tile.h)
+  bool lowp_shape(const LayerDev &y, int src_mode, int Lc, int H, int W, TileShape *t, size_t *wgs) const {
+    return prec != NPG_FP32 && y.dil == 1 && (src_mode == SRC_PLAIN || src_mode == SRC_UPCAT || src_mode == SRC_ENERGY) &&
+           tile_shape(y.cout, Lc, H, W, cap(), t, wgs);
+  }
+  // Tile of such a layer over Lc leaves of an H x W map; false where no tile
+  // fits (the output channels are no 16, 32, 64 or 128; a map narrower than 4).
+  //  - 16 columns where the map has them (a fragment is then one row and
+  //    serves three tap rows), 8 columns for 64-pixel tiles (a smaller halo)
+  //    and 8-wide maps;
+  //  - up to four blocks of 16 channels per workgroup: more would take the
+  //    pixels' registers, and a patch read feeds four products already;
+  //  - halved, pixels first, while the launch has fewer than 512 workgroups
+  //    (two per CU): a few leaves are bound by the latency of the tiles, not
+  //    by what a tile reads.  npg_reconstruct_fused of 11 leaves of 64x64 in
+  //    BF16: 155 -> 79 us.
+  static bool tile_shape(int Cout, int Lc, int H, int W, int mw_max, TileShape *t, size_t *wgs) {
+    if (Cout % 16 || Cout > 128 || (Cout & (Cout - 1)) || H < 4 || W < 4) return false;
+    int MW = mw_max, NW = std::min(Cout / 16, 4);
+    if (NW > 2) MW = std::min(MW, 4);
+    const int lim = W >= 16 ? H / 4 : W == 8 ? std::min(4, H / 2) : 1;  // whole tiles; few leaves in one
+    while (MW > lim) MW >>= 1;
+    auto tiles = [&] { return ((size_t)Lc * H * W + 64 * MW - 1) / (64 * MW) * (Cout / 16 / NW); };
+    while (tiles() < 512 && (MW > 1 || NW > 1)) {
+      if (MW > 1) MW >>= 1;
+      else NW >>= 1;
+    }
+    *wgs = tiles();
+    *t = TileShape{MW, NW, W == 4 ? 2 : W == 8 || (MW == 1 && H >= 8) ? 3 : 4};
+    return true;
+  }
+  int kc_lowp(const LayerDev &y) const { return y.cin % 32 == 0 ? 32 : 16; }
+  // LDS a workgroup may take: with up to two workgroups per CU, as many K
+  // chunks as fit are staged at once, so that a workgroup waits for memory
+  // once instead of once per chunk
+  static size_t tile_lds(size_t wgs) { return wgs <= 256 ? 160 * 1024 : wgs <= 512 ? 80 * 1024 : 0; }
+  hipError_t launch_lowp(const TileArgs &a, const TileShape &t, int kc, TileIn in) const {
+    return prec == NPG_FP8 ? launch_tile_fp8(a, t, kc, in, s) : launch_tile_bf16(a, t, kc, in, s);
+  }
   // channel granularity of the tiled kernel's 16-byte input loads
   int vec() const { return prec == NPG_FP32 ? 2 : prec == NPG_FP8 ? 16 : 8; }
   bool mfma_fits(const LayerDev &y, const Src &src, int H, int W, Tiling *t, int mw_lim = 8) const {
@@ -1829,11 +1731,15 @@ struct Runner {
     if (src.mode == SRC_UPCAT && (src.C0 % v || src.C1 % v)) return false;
     // the tiled kernel takes each K chunk's channels from one source
     const int kc = prec == NPG_FP32 ? KC32 : (y.cin % 32 == 0 ? 32 : 16);
+    TileShape ts;
+    size_t wgs;
     if (src.mode == SRC_UPCAT && src.C0 % kc) return false;
+    const size_t esz = prec == NPG_FP32 ? sizeof(double) : prec == NPG_FP8 ? 1 : 2;
+    if (lowp_shape(y, src.mode, 1, H, W, &ts, &wgs))  // a tile's leaves behind one buffer resource, as below
+      return (size_t)4 * H * W * std::max(std::max(src.C0, src.C1), y.cout) * esz < ((size_t)1 << 31);
     if (!tiling(y, H, W, t, mw_lim)) return false;
     // the tiles read their input through buffer resources: the bytes of one
     // tile's leaves must stay below 2^31 (offsets at or past 2^31 mean padding)
-    const size_t esz = prec == NPG_FP32 ? sizeof(double) : prec == NPG_FP8 ? 1 : 2;
     const size_t px = src.mode == SRC_POOL ? (size_t)4 * H * W : (size_t)H * W;
     const size_t ch = (size_t)std::max(src.C0, src.C1);
     return (size_t)t->TL * px * ch * esz < ((size_t)1 << 31);
@@ -1844,11 +1750,10 @@ struct Runner {
   bool first_fusable(const LayerDev &l0, const LayerDev &l1, int H, int W, Tiling *t) const {
     if (force_direct || amax || !fuse_first) return false;
     if (l0.k != 3 || l0.cin != 1 || l0.cout != 16 || l1.k != 3 || l1.cin != 16 || l1.cout != 16) return false;
-    if (!tiling(l1, H, W, t)) return false;
-    const size_t lds = prec == NPG_FP32  ? conv_lds_bytes<F32P>(*t, true)
-                       : prec == NPG_FP8 ? conv_lds_bytes<FP8S>(*t, true)
-                                         : conv_lds_bytes<BF16S>(*t, true);
-    return lds <= 160 * 1024;
+    TileShape ts;
+    size_t wgs;
+    if (prec != NPG_FP32) return lowp_shape(l1, SRC_ENERGY, 1, H, W, &ts, &wgs);
+    return tiling(l1, H, W, t) && conv_lds_bytes<F32P>(*t, true) <= 160 * 1024;
   }
 
   int conv_first_fused(const LayerDev &l0, const LayerDev &l1, const Src &energy, int Lc, int H, int W,
@@ -1859,6 +1764,36 @@ struct Runner {
     }
     Tiling t;
     if (!first_fusable(l0, l1, H, W, &t)) return npg_fail(ctx, NPG_E_ARG, "internal: first layer not fusable");
+    hipError_t e;
+    TileShape ts;
+    size_t wgs;
+    if (lowp_shape(l1, SRC_ENERGY, Lc, H, W, &ts, &wgs)) {
+      TileArgs a;
+      a.H = H;
+      a.W = W;
+      a.Lc = Lc;
+      a.Cin = a.Cout = a.C0 = 16;
+      a.nchunk = 1;
+      a.w = prec == NPG_FP8 ? (const void *)l1.pk8s : (const void *)l1.pk16s;
+      a.bias = l1.b;
+      a.wsc = l1.wsc8;
+      a.oinv = 1.0f / l1.a8;
+      a.asc = l1.a8;
+      a.energy = static_cast<const uint64_t *>(energy.s0);
+      a.tot = energy.tot;
+      a.w0 = l0.w;
+      a.b0 = l0.b;
+      a.oinv0 = prec == NPG_FP8 ? 1.0f / l0.a8 : 1.0f;
+      a.out = out;
+      if (pool_out && (ts.TWL != 4 || ts.MW > 1)) {
+        a.pool_out = pool_out;
+        pooled = true;
+      }
+      const double tw = 1 << ts.TWL, tr = std::min(64.0 * ts.MW / tw, (double)H);
+      ctx->conv_flops[0] += 2.0 * Lc * H * W * 16.0 * 9.0 * 16.0;
+      ctx->conv_flops[1] += 2.0 * Lc * H * W / (tr * tw) * (tr + 2.0) * (tw + 2.0) * 16.0 * 9.0;
+      e = launch_lowp(a, ts, 16, TILE_FIRST);
+    } else {
     ConvArgs a{};
     a.src = energy;
     a.Cin = 16;
@@ -1875,7 +1810,7 @@ struct Runner {
     a.fTPX = make_fastdiv((uint32_t)(t.TW * t.TR));
     a.tiles_x = W / t.TW;
     a.tiles_per_leaf = (H / t.TR) * a.tiles_x;
-    a.nchunk = prec == NPG_FP32 ? 16 / KC32 : 1;
+    a.nchunk = 16 / KC32;
     a.bias = l1.b;
     a.head_w = nullptr;
     a.wsc = l1.wsc8;
@@ -1883,7 +1818,7 @@ struct Runner {
     a.asc = l1.a8;
     a.w0 = l0.w;
     a.b0 = l0.b;
-    a.oinv0 = prec == NPG_FP8 ? 1.0f / l0.a8 : 1.0f;
+    a.oinv0 = 1.0f;
     a.out = out;
     if (pool_out && t.TR % 2 == 0 && t.TW % 2 == 0) {
       a.pool_out = pool_out;
@@ -1894,17 +1829,9 @@ struct Runner {
     // every patch pixel (the tile and its one-pixel halo)
     ctx->conv_flops[0] += 2.0 * Lc * H * W * 16.0 * 9.0 * 16.0;
     ctx->conv_flops[1] += 2.0 * tiles * t.TL * (t.TR + 2.0) * (t.TW + 2.0) * 16.0 * 9.0;
-    hipError_t e;
-    if (prec == NPG_FP32) {
-      a.wpk = l1.pk32;
-      a.wpk64 = l1.pk64;
-      e = launch_mfma<F32P>(a, t, tiles, s);
-    } else if (prec == NPG_FP8) {
-      a.wpk = l1.pk8s;
-      e = launch_mfma<FP8S>(a, t, tiles, s);
-    } else {
-      a.wpk = l1.pk16s;
-      e = launch_mfma<BF16S>(a, t, tiles, s);
+    a.wpk = l1.pk32;
+    a.wpk64 = l1.pk64;
+    e = launch_mfma<F32P>(a, t, tiles, s);
     }
     if (e != hipSuccess) return npg_fail(ctx, NPG_E_HIP, "fused first conv launch: %s", hipGetErrorString(e));
     if (ev) {
@@ -1959,6 +1886,43 @@ struct Runner {
     Tiling t;
     const bool mfma_ok = (act == ACT_RELU || act == ACT_ELU) && mfma_fits(y, src, H, W, &t, head ? 4 : 8) &&
                          (!head || y.cout == 16);
+    TileShape ts;
+    size_t wgs;
+    if (mfma_ok && lowp_shape(y, src.mode, Lc, H, W, &ts, &wgs)) {
+      const int kc = kc_lowp(y);
+      TileArgs a;
+      a.s0 = src.s0;
+      a.s1 = src.s1;
+      a.C0 = src.C0;
+      a.C1 = src.C1;
+      a.H = H;
+      a.W = W;
+      a.Lc = Lc;
+      a.Cin = y.cin;
+      a.Cout = y.cout;
+      a.nchunk = (y.cin + kc - 1) / kc;
+      a.lds_budget = tile_lds(wgs);
+      a.w = prec == NPG_FP8 ? (kc == 32 ? (const void *)y.pk8 : y.pk8s) : (kc == 32 ? (const void *)y.pk16 : y.pk16s);
+      a.bias = y.b;
+      a.head_w = head ? head->w : nullptr;
+      a.head_b = head ? m->host_b[head - &m->layer[0]][0] : 0.0f;
+      a.wsc = y.wsc8;
+      a.oinv = 1.0f / y.a8;
+      a.asc = y.a8;
+      a.act = act;
+      a.res = res;
+      a.out = out;
+      if (pool_out && !head && (ts.TWL != 4 || ts.MW > 1)) {
+        a.pool_out = pool_out;
+        pooled = true;
+      }
+      const double px = (double)Lc * H * W;
+      ctx->conv_flops[0] += 2.0 * px * y.cout * 9.0 * y.cin;
+      if (head) ctx->conv_flops[1] += 2.0 * px * head->cin;  // 1x1 head in the epilogue
+      const hipError_t e = launch_lowp(a, ts, kc, src.mode == SRC_UPCAT ? TILE_UPCAT : TILE_PLAIN);
+      if (e != hipSuccess) return npg_fail(ctx, NPG_E_HIP, "conv tile launch: %s", hipGetErrorString(e));
+      return NPG_OK;
+    }
     if (mfma_ok) {
       ConvArgs a;
       a.src = src;
