@@ -19,8 +19,8 @@
 //    consecutive channels of pixel lr, and row swaps between the lanes of two
 //    channel blocks make that 16 bytes, whole pixels per instruction; the 2x2
 //    means of the next level are formed from the same registers.
-// BF16 network on 1501 leaves of 128x128: 3591 -> 2947 us, FP8 on 1024 of 64x64:
-// 543 -> 416 us, against the tiles with run-time geometry.
+// BF16 network on 1501 leaves of 128x128: 3799 -> 2875 us, FP8 on 1024 of 64x64:
+// 544 -> 397 us, against the tiles with run-time geometry.
 //
 // Every output sums its terms in the same order whatever the tile: chunks in
 // order, then taps in order (for 16-channel chunks pairs of taps, one product
@@ -41,7 +41,7 @@ struct TileArgs {
   size_t lds_budget = 0;                    // LDS for chunks staged together; 0: one at a time
   int cstage = 1;                           // chunks staged per barrier (set by the launch)
   int TR = 0, TL = 1;                       // rows per leaf and leaves of a tile
-  int tiles_x = 1, tiles_per_leaf = 1;
+  int lw = 0, ltx = 0, ltpl = 0;            // log2 of W, of the tiles in a row and of those in a leaf
   const void *w = nullptr;                  // packed weights [chunk][tap][Cout][KC]
   const float *bias = nullptr;
   const float *head_w = nullptr;            // non-null: fuse the 1x1 head + softplus (Cout == 16)
@@ -106,6 +106,13 @@ struct TileGeom {
 
 constexpr uint32_t OOB = 0x80000000u;  // past the end of every buffer: loads give zeros
 
+// e4m3_pack4_d of values that are not negative (or NaN): only the upper clamp
+__device__ __forceinline__ uint32_t pack4_pos(float a, float b, float c, float d) {
+  auto top = [](float x) { return x > E4M3_MAX ? E4M3_MAX : x; };
+  const int lo = __builtin_amdgcn_cvt_pk_fp8_f32(top(a), top(b), 0, false);
+  return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(top(c), top(d), lo, true);
+}
+
 // value of the lane N away (N a power of two below 16): N = 1 and 8 on the
 // DPP path
 template <int N>
@@ -157,9 +164,10 @@ __global__ __launch_bounds__(256, MW * NW >= 16 ? 2 : MW * NW >= 8 ? 3 : 4) void
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int H = a.H, W = a.W, TL = G::TLMAX == 1 ? 1 : a.TL, TR = G::TLMAX == 1 ? ROWS : a.TR;
   const int Cout = a.Cout, n0 = blockIdx.y * BN;
-  const int grp = blockIdx.x / a.tiles_per_leaf, t = blockIdx.x - grp * a.tiles_per_leaf;
+  // maps are powers of two on both sides, and so are the tiles in them
+  const int lw = a.lw, grp = blockIdx.x >> a.ltpl, t = blockIdx.x & ((1 << a.ltpl) - 1);
   const int leaf0 = grp * TL;
-  const int ty0 = (t / a.tiles_x) * TR, tx0 = (t - (t / a.tiles_x) * a.tiles_x) * TW;
+  const int ty0 = (t >> a.ltx) * TR, tx0 = (t & ((1 << a.ltx) - 1)) * TW;
   const int nl = min(TL, a.Lc - leaf0);
 
   // leaf of patch row r (blocks of TR + 2 rows), at most three compares
@@ -178,26 +186,34 @@ __global__ __launch_bounds__(256, MW * NW >= 16 ? 2 : MW * NW >= 8 ? 3 : 4) void
   if constexpr (IN != TILE_FIRST) {
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
-      const int s = (wave + 4 * i) * 64 + lane;
-      const int pp = s / SPP, g = s - pp * SPP;
-      const int pr = pp / PW, pc = pp - pr * PW;
-      const int ls = leaf_of(pr, TR + 2);
-      const int y = ty0 - 1 + pr - ls * (TR + 2), x = tx0 - 1 + pc;
-      const uint32_t gs = 16u * (uint32_t)(TWO ? g : g ^ P::swz(pc));
-      const bool in = pp < npx && (uint32_t)y < (uint32_t)H && (uint32_t)x < (uint32_t)W;
+      // (products of 24-bit numbers: pixels of a tile's leaves < 2^22, bytes
+      // of a pixel <= 2^14)
+      const uint32_t s = ((uint32_t)wave * 64 + (uint32_t)lane) + 256u * i;
+      __builtin_assume(s < 8192);
+      const uint32_t pp = s / SPP, g = s - pp * SPP;
+      const uint32_t pr = pp / PW, pc = pp - pr * PW;
+      const int ls = leaf_of((int)pr, TR + 2);
+      const int y = ty0 - 1 + (int)pr - ls * (TR + 2), x = tx0 - 1 + (int)pc;
+      const uint32_t gs = 16u * (uint32_t)(TWO ? (int)g : (int)g ^ P::swz((int)pc));
+      const bool in = (int)pp < npx && (uint32_t)y < (uint32_t)H && (uint32_t)x < (uint32_t)W;
+      const uint32_t px = (uint32_t)(((ls * H + y) << lw) + x);
       if constexpr (IN == TILE_UPCAT) {
-        pu[i] = in ? (uint32_t)((ls * (H >> 1) + (y >> 1)) * (W >> 1) + (x >> 1)) * (uint32_t)(a.C0 * ESZ) + gs : OOB;
-        po[i] = in ? (uint32_t)((ls * H + y) * W + x) * (uint32_t)(a.C1 * ESZ) + gs : OOB;
+        const uint32_t pxu = (uint32_t)(((ls * (H >> 1) + (y >> 1)) << (lw - 1)) + (x >> 1));
+        const uint32_t ou = __umul24(pxu, (uint32_t)(a.C0 * ESZ)) + gs, o = __umul24(px, (uint32_t)(a.C1 * ESZ)) + gs;
+        pu[i] = in ? ou : OOB;
+        po[i] = in ? o : OOB;
       } else {
-        po[i] = in ? (uint32_t)((ls * H + y) * W + x) * (uint32_t)(a.C0 * ESZ) + gs : OOB;
+        const uint32_t o = __umul24(px, (uint32_t)(a.C0 * ESZ)) + gs;
+        po[i] = in ? o : OOB;
       }
     }
   }
 #pragma unroll
   for (int i = 0; i < NQ; ++i) {
-    const int s = (wave + 4 * i) * 64 + lane;
-    const int row = s / SPP, g = s - row * SPP, tap = row / BN, n = row - tap * BN;
-    wo[i] = tap < 9 ? (uint32_t)(tap * Cout + n) * (uint32_t)PXB + 16u * (uint32_t)(TWO ? g : g ^ P::swz(row)) : OOB;
+    const uint32_t s = ((uint32_t)wave * 64 + (uint32_t)lane) + 256u * i;
+    const uint32_t row = s / SPP, g = s - row * SPP, tap = row / BN, n = row - tap * BN;
+    const uint32_t o = (__umul24(tap, (uint32_t)Cout) + n) * PXB + 16u * (uint32_t)(TWO ? (int)g : (int)g ^ P::swz((int)row));
+    wo[i] = tap < 9 ? o : OOB;
   }
   const int wbytes = 9 * Cout * PXB;  // of one chunk
   const int cbytes = G::chunk_bytes(TL), pbytes = G::patch_bytes(TL);
@@ -353,7 +369,7 @@ __global__ __launch_bounds__(256, MW * NW >= 16 ? 2 : MW * NW >= 8 ? 3 : 4) void
           tl = a.tot[leaf0 + ls];
           inv = tl > 0.0 ? 1.0 / tl : 0.0;
         }
-        const double e = hw * (double)a.energy[((size_t)(leaf0 + ls) * H + y) * W + x];
+        const double e = hw * (double)(a.energy + (size_t)leaf0 * H * W)[(uint32_t)(((ls * H + y) << lw) + x)];
         double q = e * inv;
         q = fma(fma(-q, tl, e), inv, q);
         q = fma(fma(-q, tl, e), inv, q);
@@ -362,6 +378,14 @@ __global__ __launch_bounds__(256, MW * NW >= 16 ? 2 : MW * NW >= 8 ? 3 : 4) void
       xt[i] = v;
     }
     __syncthreads();
+    // the biases in vector registers (a product takes one scalar operand,
+    // its weight)
+    float bv[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+      bv[c] = b0[c];
+      asm("" : "+v"(bv[c]));
+    }
     for (int pp = tid; pp < npx; pp += 256) {
       const int pr = pp / PW, pc = pp - pr * PW;
       const int ls = leaf_of(pr, TR + 2);
@@ -380,14 +404,14 @@ __global__ __launch_bounds__(256, MW * NW >= 16 ? 2 : MW * NW >= 8 ? 3 : 4) void
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const int c = 4 * c4 + q;
-            float s = b0[c];
+            float s = bv[c];
 #pragma unroll
             for (int k = 0; k < 9; ++k) s = fmaf(w0[c * 9 + k], xv[k], s);
-            s = s > 0.0f ? s : 0.0f;
+            s = fmaxf(s, 0.0f);
             r[q] = P::Q8 ? s * a.oinv0 : s;
           }
           if constexpr (P::Q8) {
-            o[c4] = e4m3_pack4_d(r[0], r[1], r[2], r[3]);
+            o[c4] = pack4_pos(r[0], r[1], r[2], r[3]);
           } else {
             o[2 * c4] = (uint32_t)f2bf(r[0]) | ((uint32_t)f2bf(r[1]) << 16);
             o[2 * c4 + 1] = (uint32_t)f2bf(r[2]) | ((uint32_t)f2bf(r[3]) << 16);
@@ -440,9 +464,9 @@ __global__ __launch_bounds__(256, MW * NW >= 16 ? 2 : MW * NW >= 8 ? 3 : 4) void
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const float v0 = acc[mi][0][r] * ws[r] + bn[r];
-          q[r] = (v0 > 0.0f ? v0 : 0.0f) * a.oinv;
+          q[r] = fmaxf(v0, 0.0f) * a.oinv;
         }
-        const int pk = (int)e4m3_pack4_d(q[0], q[1], q[2], q[3]);
+        const int pk = (int)pack4_pos(q[0], q[1], q[2], q[3]);
         const auto d01 = __builtin_amdgcn_cvt_pk_f32_fp8(pk, false), d23 = __builtin_amdgcn_cvt_pk_f32_fp8(pk, true);
         const float dq[4] = {d01[0], d01[1], d23[0], d23[1]};
 #pragma unroll
@@ -451,7 +475,7 @@ __global__ __launch_bounds__(256, MW * NW >= 16 ? 2 : MW * NW >= 8 ? 3 : 4) void
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const float v0 = acc[mi][0][r] + bn[r];
-          v += bf2f(f2bf(v0 > 0.0f ? v0 : 0.0f)) * hw[r];
+          v += bf2f(f2bf(fmaxf(v0, 0.0f))) * hw[r];
         }
       }
       v += __shfl_xor(v, 16);
@@ -462,7 +486,7 @@ __global__ __launch_bounds__(256, MW * NW >= 16 ? 2 : MW * NW >= 8 ? 3 : 4) void
 #pragma unroll
     for (int h = 0; h < (MW + 3) / 4; ++h)
       if (4 * h + lg < MW)
-        out[(uint32_t)((y0 + (4 * h + lg) * FR) * W + tx0 + col)] = softplus_f(mine[h] + a.head_b);
+        out[(uint32_t)(((y0 + (4 * h + lg) * FR) << lw) + tx0 + col)] = softplus_f(mine[h] + a.head_b);
     return;
   }
   // packed outputs: NWD words (16 bytes where the tile has the channels) of
@@ -490,13 +514,14 @@ __global__ __launch_bounds__(256, MW * NW >= 16 ? 2 : MW * NW >= 8 ? 3 : 4) void
         for (int r = 0; r < 4; ++r) {
           if constexpr (P::Q8) {
             const float x = acc[mi][ni][r] * ws[ni][r] + bn[ni][r];
-            q[r] = (x > 0.0f ? x : 0.0f) * a.oinv;
+            q[r] = fmaxf(x, 0.0f) * a.oinv;
           } else {
-            q[r] = act_fn(acc[mi][ni][r] + bn[ni][r], X ? a.act : ACT_RELU);
+            const float x = acc[mi][ni][r] + bn[ni][r];
+            q[r] = X ? act_fn(x, a.act) : fmaxf(x, 0.0f);
           }
         }
         if constexpr (P::Q8) {
-          pk[ni][0] = e4m3_pack4_d(q[0], q[1], q[2], q[3]);
+          pk[ni][0] = pack4_pos(q[0], q[1], q[2], q[3]);
         } else {
           pk[ni][0] = (uint32_t)f2bf(q[0]) | ((uint32_t)f2bf(q[1]) << 16);
           pk[ni][1] = (uint32_t)f2bf(q[2]) | ((uint32_t)f2bf(q[3]) << 16);
@@ -543,7 +568,7 @@ __global__ __launch_bounds__(256, MW * NW >= 16 ? 2 : MW * NW >= 8 ? 3 : 4) void
   };
 #pragma unroll
   for (int mi = 0; mi < MW; ++mi) {
-    const uint32_t o = ((uint32_t)((y0 + mi * FR) * W + tx0 + col) * (uint32_t)Cout + (uint32_t)(n0 + chb)) * ESZ;
+    const uint32_t o = __umul24((uint32_t)(((y0 + mi * FR) << lw) + tx0 + col), (uint32_t)(Cout * ESZ)) + (uint32_t)(n0 + chb) * ESZ;
 #pragma unroll
     for (int p = 0; p < NPC; ++p) {
       if constexpr (X) {
@@ -559,24 +584,39 @@ __global__ __launch_bounds__(256, MW * NW >= 16 ? 2 : MW * NW >= 8 ? 3 : 4) void
   if (a.pool_out && (TWL != 4 || MW > 1)) {
     // the 2x2 means, stored [leaf][H/2][W/2][Cout]: the neighbouring column
     // is the lane next door, the row below another lane (fragments of
-    // several rows) or this lane's next fragment
+    // several rows) or this lane's next fragment.  The two lanes of a window
+    // form half of its words each: the even lane the first half.
     char *po2 = static_cast<char *>(a.pool_out) + (size_t)leaf0 * (H >> 1) * (W >> 1) * Cout * ESZ;
-    constexpr int ST = FR == 1 ? 2 : 1;
+    constexpr int ST = FR == 1 ? 2 : 1, NH = NWD == 1 ? 1 : NWD / 2;
+    const bool odd = lr & 1;
 #pragma unroll
     for (int mi = 0; mi < MW; mi += ST)
 #pragma unroll
       for (int p = 0; p < NPC; ++p) {
-        uint32_t m[NWD];
+        uint32_t m[NH];
 #pragma unroll
-        for (int k = 0; k < NWD; ++k) {
-          const uint32_t x = v[mi][p][k], z = FR == 1 ? v[mi + ST - 1][p][k] : xor_lane<FR == 2 ? 8 : 4>(x);
-          m[k] = pool_word<P>(x, xor_lane<1>(x), z, xor_lane<1>(z));
+        for (int k = 0; k < NH; ++k) {
+          auto row_below = [&](uint32_t x, int w) { return FR == 1 ? v[mi + ST - 1][p][w] : xor_lane<FR == 2 ? 8 : 4>(x); };
+          const uint32_t x0 = v[mi][p][k], z0 = row_below(x0, k);
+          if constexpr (NWD == 1) {
+            m[k] = pool_word<P>(x0, xor_lane<1>(x0), z0, xor_lane<1>(z0));
+          } else {
+            const uint32_t x1 = v[mi][p][k + NH], z1 = row_below(x1, k + NH);
+            const uint32_t xo = odd ? x1 : x0, zo = odd ? z1 : z0;  // this lane's half of the words ...
+            const uint32_t xn = xor_lane<1>(odd ? x0 : x1), zn = xor_lane<1>(odd ? z0 : z1);  // ... from next door
+            m[k] = pool_word<P>(odd ? xn : xo, odd ? xo : xn, odd ? zn : zo, odd ? zo : zn);
+          }
         }
         const int y = y0 + mi * FR;  // even in the lanes that store
-        if (!(lr & 1) && (FR == 1 || !((lr >> TWL) & 1)))
-          put(po2 + ((uint32_t)((y >> 1) * (W >> 1) + ((tx0 + col) >> 1)) * (uint32_t)Cout + (uint32_t)(n0 + chb)) * ESZ +
-                  32 * ESZ * p,
-              m);
+        if ((NWD > 1 || !odd) && (FR == 1 || !((lr >> TWL) & 1))) {
+          char *d = po2 + __umul24((uint32_t)(((y >> 1) << (lw - 1)) + ((tx0 + col) >> 1)), (uint32_t)(Cout * ESZ)) +
+                    (uint32_t)(n0 + chb) * ESZ + 32 * ESZ * p + (odd ? 4 * NH : 0);
+          if constexpr (NH == 1) {
+            *reinterpret_cast<uint32_t *>(d) = m[0];
+          } else {
+            *reinterpret_cast<uint2 *>(d) = make_uint2(m[0], m[1]);
+          }
+        }
       }
   }
 }
@@ -590,9 +630,11 @@ hipError_t launch_tile_kx(TileArgs &a, hipStream_t s) {
   if (a.W % G::TW || a.H % a.TR || a.TL > G::TLMAX || MW * G::FR > a.TR || a.Cout % G::BN)
     return hipErrorInvalidValue;
   if (a.pool_out && TWL == 4 && MW == 1) return hipErrorInvalidValue;
-  a.tiles_x = a.W / G::TW;
-  a.tiles_per_leaf = (a.H / a.TR) * a.tiles_x;
-  const size_t tiles = (size_t)((a.Lc + a.TL - 1) / a.TL) * a.tiles_per_leaf;
+  if ((a.H & (a.H - 1)) || (a.W & (a.W - 1)) || a.H > 1024 || a.W > 1024) return hipErrorInvalidValue;
+  a.lw = __builtin_ctz(a.W);
+  a.ltx = __builtin_ctz(a.W / G::TW);
+  a.ltpl = a.ltx + __builtin_ctz(a.H / a.TR);
+  const size_t tiles = (size_t)((a.Lc + a.TL - 1) / a.TL) << a.ltpl;
   if (tiles > 0x7fffffffu) return hipErrorInvalidValue;
   const size_t cb = (size_t)G::chunk_bytes(a.TL);
   size_t lds = cb;

@@ -1658,6 +1658,11 @@ struct Runner {
   int upsample_taps9 = 0;                    // 1: upsampled channels with nine taps (testing)
   const std::vector<int> *mw_cap = nullptr;  // per conv call of a chunk (autotuned)
   int mw_all = 4;                            // cap for every call (autotuner probes)
+  // cap for an 8/16-bit first layer: its tiles live on the vector ALUs, which
+  // compute the first layer on their halo too, 1.20 patch pixels per output
+  // pixel in 512-pixel tiles against 1.27 (BF16 1024 leaves of 128x128, this
+  // layer: 308 against 330 us)
+  int mw_first = 8;
   std::vector<hipEvent_t> *ev = nullptr;     // per-call begin/end events (autotuner)
   int call = 0;                              // conv call index within a chunk
   int fuse_first = 1;                        // first layer inside the second layer's staging
@@ -1666,8 +1671,8 @@ struct Runner {
                                              // (float bits); the head is then not fused
   bool pooled = false;                       // the last conv also stored its output's 2x2 means
 
-  int cap() const {
-    int c = mw_all;
+  int cap() const { return cap_of(mw_all); }
+  int cap_of(int c) const {
     if (mw_cap && call < (int)mw_cap->size()) c = std::min(c, (*mw_cap)[call]);
     return c;
   }
@@ -1686,8 +1691,9 @@ struct Runner {
   // 8/16-bit layers on plain or concatenated inputs, whole 3x3 taps one pixel
   // apart: the tiles with compile-time geometry (conv_tile.h)
   bool lowp_shape(const LayerDev &y, int src_mode, int Lc, int H, int W, TileShape *t, size_t *wgs) const {
+    const int c = src_mode == SRC_ENERGY ? cap_of(mw_first) : cap();
     return prec != NPG_FP32 && y.dil == 1 && (src_mode == SRC_PLAIN || src_mode == SRC_UPCAT || src_mode == SRC_ENERGY) &&
-           tile_shape(y.cout, Lc, H, W, cap(), t, wgs);
+           tile_shape(y.cout, Lc, H, W, c, t, wgs);
   }
   // Tile of such a layer over Lc leaves of an H x W map; false where no tile
   // fits (the output channels are no 16, 32, 64 or 128; a map narrower than 4).
@@ -2371,6 +2377,7 @@ Runner make_runner(npg_ctx *ctx, const npg_model *m, npg_precision prec, hipStre
   R.pool_outputs = ctx->opt("pool_outputs", 1) ? 1 : 0;
   const long long cap = ctx->opt("tile_cap", 4);  // testing: pixel tiles of at most 64 * cap
   R.mw_all = cap >= 8 ? 8 : cap >= 4 ? 4 : cap >= 2 ? 2 : 1;
+  if (ctx->opts.count("tile_cap")) R.mw_first = R.mw_all;
   return R;
 }
 
@@ -2399,7 +2406,7 @@ void apply_tune(npg_ctx *ctx, Runner &R, int H, int W, std::vector<int> *hold) {
   if (it != ctx->tune.end() && it->second.size() > 1) {
     hold->assign(it->second.begin() + 1, it->second.end());
     R.mw_cap = hold;
-    R.mw_all = 8;  // the table's picks (up to 8, as probed) cap each call
+    R.mw_all = R.mw_first = 8;  // the table's picks (up to 8, as probed) cap each call
   }
 }
 
@@ -2777,7 +2784,7 @@ extern "C" int npg_autotune(npg_ctx *ctx, const npg_model *m, int H, int W, npg_
   std::vector<int> pick(ncall, 4);
   int err = NPG_OK;
   for (int ci = 0; ci < 4 && !err; ++ci) {
-    R.mw_all = caps[ci];
+    R.mw_all = R.mw_first = caps[ci];
     R.ev = nullptr;
     err = net_chunk(R, in, (int)probe, H, W, dens, B);  // warm-up
     for (int rep = 0; rep < 3 && !err; ++rep) {
@@ -2796,6 +2803,7 @@ extern "C" int npg_autotune(npg_ctx *ctx, const npg_model *m, int H, int W, npg_
   }
   R.ev = nullptr;
   R.mw_all = 4;
+  R.mw_first = 8;
   R.mw_cap = &pick;
   // chunk size
   int best_chunk = (int)probe;
