@@ -1663,6 +1663,7 @@ struct Runner {
   // pixel in 512-pixel tiles against 1.27 (BF16 1024 leaves of 128x128, this
   // layer: 308 against 330 us)
   int mw_first = 8;
+  int mw_narrow = 2;  // cap for FP64 layers of up to 32 channels (see tiling); 0: none
   std::vector<hipEvent_t> *ev = nullptr;     // per-call begin/end events (autotuner)
   int call = 0;                              // conv call index within a chunk
   int fuse_first = 1;                        // first layer inside the second layer's staging
@@ -1678,15 +1679,26 @@ struct Runner {
   }
   // mw_lim: 4 for a fused head (its epilogue keeps one pixel per lane of a
   // 16-lane group, 4*MW <= 16)
-  bool tiling(const LayerDev &y, int H, int W, Tiling *t, int mw_lim = 8) const {
-    const int c = std::min(cap(), mw_lim);
-    if (prec == NPG_FP32) return pick_tiling<F32P>(y.cout, H, W, t, c, y.dil);
-    if (prec == NPG_FP8) {
-      if (y.cin % KC8 == 0) return pick_tiling<FP8P>(y.cout, H, W, t, c, y.dil);
-      return pick_tiling<FP8S>(y.cout, H, W, t, c, y.dil);
-    }
-    if (y.cin % KC16 == 0) return pick_tiling<BF16P>(y.cout, H, W, t, c, y.dil);
-    return pick_tiling<BF16S>(y.cout, H, W, t, c, y.dil);
+  // FP64 tiles of up to 32 channels default to 128 pixels, except the one that
+  // computes the first layer into its patch: their patch then has at most one
+  // pixel per thread, which the next chunk's load needs to run behind the
+  // products (U-Net on 1024 leaves of 64x64: 5334 -> 5097 us); and they shrink while
+  // the launch has fewer than 512 workgroups, as the 8/16-bit tiles do
+  bool tiling(const LayerDev &y, int Lc, int H, int W, Tiling *t, int mw_lim = 8, bool first = false) const {
+    auto pick = [&](int mw, Tiling *o) {
+      if (prec == NPG_FP32) return pick_tiling<F32P>(y.cout, H, W, o, mw, y.dil);
+      if (prec == NPG_FP8)
+        return y.cin % KC8 == 0 ? pick_tiling<FP8P>(y.cout, H, W, o, mw, y.dil)
+                                : pick_tiling<FP8S>(y.cout, H, W, o, mw, y.dil);
+      return y.cin % KC16 == 0 ? pick_tiling<BF16P>(y.cout, H, W, o, mw, y.dil)
+                               : pick_tiling<BF16S>(y.cout, H, W, o, mw, y.dil);
+    };
+    int c = std::min(cap(), mw_lim);
+    if (prec == NPG_FP32 && mw_narrow && y.cout <= 32 && !first) c = std::min(c, mw_narrow);
+    if (!pick(c, t)) return false;
+    Tiling n;
+    while (t->MW > 1 && (size_t)Lc * H * W < (size_t)512 * 64 * t->MW && pick(t->MW / 2, &n)) *t = n;
+    return true;
   }
   // 8/16-bit layers on plain or concatenated inputs, whole 3x3 taps one pixel
   // apart: the tiles with compile-time geometry (conv_tile.h)
@@ -1731,7 +1743,7 @@ struct Runner {
   }
   // channel granularity of the tiled kernel's 16-byte input loads
   int vec() const { return prec == NPG_FP32 ? 2 : prec == NPG_FP8 ? 16 : 8; }
-  bool mfma_fits(const LayerDev &y, const Src &src, int H, int W, Tiling *t, int mw_lim = 8) const {
+  bool mfma_fits(const LayerDev &y, const Src &src, int Lc, int H, int W, Tiling *t, int mw_lim = 8) const {
     const int v = vec();
     if (force_direct || y.k != 3 || src.mode == SRC_ENERGY || src.mode == SRC_FIVE || y.cin % v) return false;
     if (src.mode == SRC_UPCAT && (src.C0 % v || src.C1 % v)) return false;
@@ -1743,7 +1755,7 @@ struct Runner {
     const size_t esz = prec == NPG_FP32 ? sizeof(double) : prec == NPG_FP8 ? 1 : 2;
     if (lowp_shape(y, src.mode, 1, H, W, &ts, &wgs))  // a tile's leaves behind one buffer resource, as below
       return (size_t)4 * H * W * std::max(std::max(src.C0, src.C1), y.cout) * esz < ((size_t)1 << 31);
-    if (!tiling(y, H, W, t, mw_lim)) return false;
+    if (!tiling(y, Lc, H, W, t, mw_lim)) return false;
     // the tiles read their input through buffer resources: the bytes of one
     // tile's leaves must stay below 2^31 (offsets at or past 2^31 mean padding)
     const size_t px = src.mode == SRC_POOL ? (size_t)4 * H * W : (size_t)H * W;
@@ -1753,13 +1765,13 @@ struct Runner {
 
   // The first layer (energy -> 16 channels, 3x3, ReLU) can be computed inside
   // the second layer's patch staging (16 -> 16, 3x3, ReLU) when the tiles fit.
-  bool first_fusable(const LayerDev &l0, const LayerDev &l1, int H, int W, Tiling *t) const {
+  bool first_fusable(const LayerDev &l0, const LayerDev &l1, int Lc, int H, int W, Tiling *t) const {
     if (force_direct || amax || !fuse_first) return false;
     if (l0.k != 3 || l0.cin != 1 || l0.cout != 16 || l1.k != 3 || l1.cin != 16 || l1.cout != 16) return false;
     TileShape ts;
     size_t wgs;
     if (prec != NPG_FP32) return lowp_shape(l1, SRC_ENERGY, 1, H, W, &ts, &wgs);
-    return tiling(l1, H, W, t) && conv_lds_bytes<F32P>(*t, true) <= 160 * 1024;
+    return tiling(l1, Lc, H, W, t, 8, true) && conv_lds_bytes<F32P>(*t, true) <= 160 * 1024;
   }
 
   int conv_first_fused(const LayerDev &l0, const LayerDev &l1, const Src &energy, int Lc, int H, int W,
@@ -1769,7 +1781,7 @@ struct Runner {
       if (hipEventRecord((*ev)[2 * call], s) != hipSuccess) return npg_fail(ctx, NPG_E_HIP, "event record");
     }
     Tiling t;
-    if (!first_fusable(l0, l1, H, W, &t)) return npg_fail(ctx, NPG_E_ARG, "internal: first layer not fusable");
+    if (!first_fusable(l0, l1, Lc, H, W, &t)) return npg_fail(ctx, NPG_E_ARG, "internal: first layer not fusable");
     hipError_t e;
     TileShape ts;
     size_t wgs;
@@ -1890,7 +1902,7 @@ struct Runner {
     if ((act == ACT_ELU || res || y.dil != 1) && (prec == NPG_FP8 || head))
       return npg_fail(ctx, NPG_E_ARG, "internal: ELU, residual and dilated layers run in FP32 or BF16, unfused");
     Tiling t;
-    const bool mfma_ok = (act == ACT_RELU || act == ACT_ELU) && mfma_fits(y, src, H, W, &t, head ? 4 : 8) &&
+    const bool mfma_ok = (act == ACT_RELU || act == ACT_ELU) && mfma_fits(y, src, Lc, H, W, &t, head ? 4 : 8) &&
                          (!head || y.cout == 16);
     TileShape ts;
     size_t wgs;
@@ -2256,7 +2268,7 @@ int net_chunk(Runner &R, const Src &in, int Lc, int H, int W, float *dens, const
     char *bufs[2] = {B.tA, B.tB};
     int i0 = 0;
     Tiling tf;
-    if (n > 2 && R.first_fusable(m->layer[0], m->layer[1], H, W, &tf)) {
+    if (n > 2 && R.first_fusable(m->layer[0], m->layer[1], Lc, H, W, &tf)) {
       rc = R.conv_first_fused(m->layer[0], m->layer[1], in, Lc, H, W, bufs[1]);
       if (rc) return rc;
       cur = plain(bufs[1], 16, dq(m->layer[1]));
@@ -2291,7 +2303,7 @@ int net_chunk(Runner &R, const Src &in, int Lc, int H, int W, float *dens, const
     // the level's output tile also stores its 2x2 means, the next level's input
     void *po = d < D - 1 && R.pool_outputs && !B.pool.empty() ? (void *)B.pool[d] : nullptr;
     Tiling tf;
-    if (d == 0 && R.first_fusable(la, lb, h, w, &tf)) {
+    if (d == 0 && R.first_fusable(la, lb, Lc, h, w, &tf)) {
       rc = R.conv_first_fused(la, lb, sa, Lc, h, w, ob, po);
       if (rc) return rc;
     } else {
@@ -2319,7 +2331,7 @@ int net_chunk(Runner &R, const Src &in, int Lc, int H, int W, float *dens, const
     if (d == 0) {
       const LayerDev &hd = m->layer[li];
       Tiling t;
-      const bool fuse = !R.amax && lb.cout == 16 && R.mfma_fits(lb, sb, h, w, &t, 4);
+      const bool fuse = !R.amax && lb.cout == 16 && R.mfma_fits(lb, sb, Lc, h, w, &t, 4);
       if (fuse) {
         rc = R.conv(lb, sb, Lc, h, w, dens, &hd, ACT_RELU);
         if (rc) return rc;
@@ -2377,7 +2389,10 @@ Runner make_runner(npg_ctx *ctx, const npg_model *m, npg_precision prec, hipStre
   R.pool_outputs = ctx->opt("pool_outputs", 1) ? 1 : 0;
   const long long cap = ctx->opt("tile_cap", 4);  // testing: pixel tiles of at most 64 * cap
   R.mw_all = cap >= 8 ? 8 : cap >= 4 ? 4 : cap >= 2 ? 2 : 1;
-  if (ctx->opts.count("tile_cap")) R.mw_first = R.mw_all;
+  if (ctx->opts.count("tile_cap")) {
+    R.mw_first = R.mw_all;
+    R.mw_narrow = 0;
+  }
   return R;
 }
 
@@ -2407,6 +2422,7 @@ void apply_tune(npg_ctx *ctx, Runner &R, int H, int W, std::vector<int> *hold) {
     hold->assign(it->second.begin() + 1, it->second.end());
     R.mw_cap = hold;
     R.mw_all = R.mw_first = 8;  // the table's picks (up to 8, as probed) cap each call
+    R.mw_narrow = 0;
   }
 }
 
@@ -2785,6 +2801,7 @@ extern "C" int npg_autotune(npg_ctx *ctx, const npg_model *m, int H, int W, npg_
   int err = NPG_OK;
   for (int ci = 0; ci < 4 && !err; ++ci) {
     R.mw_all = R.mw_first = caps[ci];
+    R.mw_narrow = 0;
     R.ev = nullptr;
     err = net_chunk(R, in, (int)probe, H, W, dens, B);  // warm-up
     for (int rep = 0; rep < 3 && !err; ++rep) {
