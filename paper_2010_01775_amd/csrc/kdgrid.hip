@@ -7,26 +7,39 @@
 //   1. voxel id of each photon (FP64 rule; invalid voxels get a sentinel
 //      key), stable radix sort of (voxel, photon index): the photons of a
 //      voxel become one contiguous segment, in ascending photon index;
-//   2. segment starts = the roots, in ascending voxel id;
+//   2. segment starts = the roots, in ascending voxel id: a bit per photon
+//      marks the first of its segment, and the rank of a root is a scan over
+//      the words of that bitmap;
 //   3. per level: the split test of each node (count, and the normal
 //      variance from exact integer sums) and, for a splitting node, the
 //      median coordinate on the longest axis by an exact radix select over
-//      its segment (8 bits per pass from the highest bit where the node's
-//      keys differ), one wavefront per node of up to 2048 photons and one
-//      workgroup per larger node; then a stable partition of each
+//      its segment (from the highest bit where the node's keys differ), one
+//      wavefront per node of up to 2048 photons and one workgroup per larger
+//      node; then a stable partition of each
 //      splitting node's segment into its two child segments, in place
 //      (child slots from a scan of the split flags, so node ids do not
 //      depend on scheduling); a node that does not split keeps its segment
 //      where it is and becomes a leaf;
-//   4. leaves sorted by segment start: depth-first order inside a voxel,
-//      voxels ascending, since every split keeps its children inside the
-//      parent's segment, first child first.
+//   4. leaves ranked by segment start, with a bitmap again: depth-first
+//      order inside a voxel, voxels ascending, since every split keeps its
+//      children inside the parent's segment, first child first.
+// The number of nodes of a level stays on the device (LevelState): the
+// kernels of all levels are queued at once, with grids that stride over
+// however many nodes there are, and the host waits once, at the end.  Waiting
+// for each level's count cost 60 us a level, as much as a level's work from
+// the fourth on.  20 million photons in 100^3 voxels, depth 8, with 2 million
+// locations: 3.98 -> 2.84 ms, together with the bitmaps (250 us of flags and
+// scans over the photons -> 60), wavefronts instead of workgroups for small
+// nodes in the partition (250 -> 100 us a level where 300 thousand nodes hold
+// the photons), 1024 threads for large ones, and photons copied into voxel
+// order by the first level (the others' selections 150 -> 90 us).
 // Point location: voxel id, then down the tree by the split comparisons.
 #include "npg_internal.h"
 
 namespace {
 
 constexpr int KD_THREADS = 256;
+constexpr int KD_BIG = 1024;  // workgroups that take one large node
 constexpr uint32_t KD_NONE = 0xFFFFFFFFu;
 constexpr double KD_QSCALE = 1048576.0;  // normals quantised to multiples of 2^-20
 
@@ -99,14 +112,59 @@ __global__ __launch_bounds__(256) void kd_keys_kernel(GridDev g, const float *__
   }
 }
 
-// flag[i] = 1 at the first photon of each valid voxel's segment; *nvalid =
-// number of photons in valid voxels (the sentinel keys sort last)
+// What a build keeps on the device about a level, and about the whole.
+struct LevelState {
+  uint32_t active;     // nodes
+  uint32_t leaf_base;  // leaves of the levels above
+  uint32_t nodes;      // node ids given out up to and including this level
+  uint32_t nbig;       // nodes of more than KD_WAVE_MAX photons
+  uint32_t nsplit;     // nodes that split
+};
+struct BuildState {
+  uint32_t nvalid;  // photons in valid voxels
+  uint32_t roots;
+  uint32_t over;  // a level did not fit max_leaves
+  uint32_t err;   // the error word when the build ended
+  LevelState lv[18];  // level max_depth + 1 (at most 17) holds the totals
+};
+
+// bits: 1 at the first photon of each valid voxel's segment; cnt[w] = number
+// of bits of word w; *nvalid = number of photons in valid voxels (the
+// sentinel keys sort last); iota (or null) receives 0, 1, ...  A wavefront takes
+// SEG_G groups of 64 keys.
+constexpr int SEG_G = 8;
 __global__ __launch_bounds__(256) void kd_seg_kernel(const uint32_t *__restrict__ ks, uint64_t n, uint32_t sent,
-                                                     uint32_t *__restrict__ flag, uint32_t *nvalid) {
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-    const uint32_t k = ks[i];
-    flag[i] = (k != sent && (i == 0 || ks[i - 1] != k)) ? 1u : 0u;
-    if (k != sent && (i + 1 == n || ks[i + 1] == sent)) *nvalid = (uint32_t)(i + 1);
+                                                     uint32_t *__restrict__ bits, uint32_t *__restrict__ cnt,
+                                                     uint32_t *__restrict__ iota, BuildState *st) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t nw = (n + 31) / 32, span = 64 * SEG_G;
+  for (uint64_t i0 = (blockIdx.x * 4ull + (threadIdx.x >> 6)) * span; i0 < n; i0 += (uint64_t)gridDim.x * 4 * span) {
+    uint32_t k[SEG_G];
+#pragma unroll
+    for (int g = 0; g < SEG_G; ++g) {
+      const uint64_t i = i0 + 64 * g + lane;
+      k[g] = i < n ? ks[i] : sent;
+    }
+    uint32_t before = i0 ? ks[i0 - 1] : KD_NONE;  // KD_NONE: no voxel id and not the sentinel
+    uint32_t word = 0;
+#pragma unroll
+    for (int g = 0; g < SEG_G; ++g) {
+      const uint64_t i = i0 + 64 * g + lane;
+      const uint32_t up = __shfl_up(k[g], 1), prev = lane ? up : before;
+      before = __shfl(k[g], 63);
+      const uint64_t m = __ballot(i < n && k[g] != sent && k[g] != prev);
+      if ((lane >> 1) == g) word = (uint32_t)(lane & 1 ? m >> 32 : m);
+      if (i < n) {
+        if (iota) iota[i] = (uint32_t)i;
+        if (k[g] == sent && prev != sent && i) st->nvalid = (uint32_t)i;
+        if (k[g] != sent && i + 1 == n) st->nvalid = (uint32_t)n;
+      }
+    }
+    const uint64_t w = i0 / 32 + lane;
+    if (lane < 2 * SEG_G && w < nw) {
+      bits[w] = word;
+      cnt[w] = (uint32_t)__popc(word);
+    }
   }
 }
 
@@ -121,34 +179,67 @@ struct Level {
   double *box;  // [6] per node: lo xyz, hi xyz
 };
 
-// roots: node j = j-th valid non-empty voxel
+// roots: node j = j-th valid non-empty voxel; rank[w] = set bits before word
+// w, rank[nw] = all of them.  More roots than max_leaves: none is written.
 __global__ __launch_bounds__(256) void kd_roots_kernel(GridDev g, const uint32_t *__restrict__ ks,
-                                                       const uint32_t *__restrict__ flag,
-                                                       const uint32_t *__restrict__ seg, uint64_t n,
-                                                       Level lv, int32_t *__restrict__ cell_root) {
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-    if (!flag[i]) continue;
-    const uint32_t j = seg[i], v = ks[i];
-    lv.start[j] = (uint32_t)i;
-    lv.id[j] = j;
-    cell_root[v] = (int32_t)j;
-    const uint32_t r = (uint32_t)g.res;
-    const uint32_t c[3] = {v % r, (v / r) % r, v / (r * r)};
+                                                       const uint32_t *__restrict__ bits,
+                                                       const uint32_t *__restrict__ rank, uint64_t nw, uint32_t cap,
+                                                       Level lv, int32_t *__restrict__ cell_root, BuildState *st) {
+  const uint32_t n0 = rank[nw];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->roots = n0;
+    st->over = n0 > cap ? 1u : 0u;
+    st->lv[0].active = n0 > cap ? 0u : n0;
+    st->lv[0].nodes = n0;
+  }
+  if (n0 > cap) return;
+  for (uint64_t w = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; w < nw; w += (uint64_t)gridDim.x * blockDim.x) {
+    uint32_t b = bits[w], j = b ? rank[w] : 0;
+    for (; b; b &= b - 1, ++j) {
+      const uint32_t i = (uint32_t)(32 * w) + (uint32_t)__builtin_ctz(b), v = ks[i];
+      lv.start[j] = i;
+      lv.id[j] = j;
+      cell_root[v] = (int32_t)j;
+      const uint32_t r = (uint32_t)g.res;
+      const uint32_t c[3] = {v % r, (v / r) % r, v / (r * r)};
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      lv.box[6 * (size_t)j + a] = __dadd_rn((double)g.lo[a], __dmul_rn((double)c[a], g.step[a]));
-      lv.box[6 * (size_t)j + 3 + a] = __dadd_rn((double)g.lo[a], __dmul_rn((double)(c[a] + 1), g.step[a]));
+      for (int a = 0; a < 3; ++a) {
+        lv.box[6 * (size_t)j + a] = __dadd_rn((double)g.lo[a], __dmul_rn((double)c[a], g.step[a]));
+        lv.box[6 * (size_t)j + 3 + a] = __dadd_rn((double)g.lo[a], __dmul_rn((double)(c[a] + 1), g.step[a]));
+      }
     }
   }
 }
 
-__global__ __launch_bounds__(256) void kd_root_counts_kernel(Level lv, uint32_t n0, const uint32_t *nvalid) {
-  const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < n0) lv.count[j] = (j + 1 < n0 ? lv.start[j + 1] : *nvalid) - lv.start[j];
+// Nodes of more than KD_WAVE_MAX photons take a whole workgroup in the
+// selection (those of a level are listed in `big`); smaller ones one wavefront
+// each.
+constexpr uint32_t KD_WAVE_MAX = 2048;
+
+__device__ __forceinline__ void note_big(uint32_t count, uint32_t j, LevelState *ls, uint32_t *big) {
+  if (count > KD_WAVE_MAX) big[atomicAdd(&ls->nbig, 1u)] = j;
+}
+
+__global__ __launch_bounds__(256) void kd_root_counts_kernel(Level lv, BuildState *st, uint32_t *__restrict__ big) {
+  const uint32_t n0 = st->lv[0].active, nvalid = st->nvalid;
+  for (uint32_t j = blockIdx.x * blockDim.x + threadIdx.x; j < n0; j += gridDim.x * blockDim.x) {
+    const uint32_t c = (j + 1 < n0 ? lv.start[j + 1] : nvalid) - lv.start[j];
+    lv.count[j] = c;
+    note_big(c, j, &st->lv[0], big);
+  }
+}
+
+// perm from places in voxel order (idx) and the photons in that order
+__global__ __launch_bounds__(256) void kd_final_kernel(const uint32_t *__restrict__ order,
+                                                       const uint32_t *__restrict__ idx, uint64_t n,
+                                                       const BuildState *st, uint32_t *__restrict__ perm) {
+  const uint32_t nvalid = st->nvalid;
+  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
+    perm[i] = order[i < nvalid ? idx[i] : (uint32_t)i];
 }
 
 // Workgroup-wide sums of three int64 values (exact, so the order is free).
-__device__ __forceinline__ void wg_sum3_i64(long long v[3], long long (*red)[KD_THREADS / 64]) {
+__device__ __forceinline__ void wg_sum3_i64(long long v[3], long long (*red)[KD_BIG / 64]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
@@ -161,7 +252,7 @@ __device__ __forceinline__ void wg_sum3_i64(long long v[3], long long (*red)[KD_
   for (int a = 0; a < 3; ++a) {
     long long t = 0;
 #pragma unroll
-    for (int w = 0; w < KD_THREADS / 64; ++w) t += red[a][w];
+    for (int w = 0; w < KD_BIG / 64; ++w) t += red[a][w];
     v[a] = t;
   }
 }
@@ -176,12 +267,21 @@ __device__ __forceinline__ bool variance_exceeds(long long sx_, long long sy_, l
   return __dsub_rn(1.0, __ddiv_rn(num, den)) > split_var;
 }
 
+// three floats in one access, at any 4-byte boundary
+typedef float f32x3 __attribute__((ext_vector_type(3), aligned(4)));
+__device__ __forceinline__ f32x3 load3(const float *p, uint32_t i) {
+  return *reinterpret_cast<const f32x3 *>(p + 3 * (size_t)i);
+}
+__device__ __forceinline__ void store3(float *p, uint32_t i, f32x3 v) {
+  *reinterpret_cast<f32x3 *>(p + 3 * (size_t)i) = v;
+}
+
 // One photon's quantised normal added to s[3]; a non-finite component counts
 // as 0 and sets *bad.
-__device__ __forceinline__ void add_qnormal(const float *__restrict__ nrm, uint32_t ph, long long s[3], bool *bad) {
+__device__ __forceinline__ void add_qnormal(f32x3 n, long long s[3], bool *bad) {
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const float v = nrm[3 * (size_t)ph + a];
+    const float v = n[a];
     if (!isfinite(v)) *bad = true;
     const double c = isfinite(v) ? fmin(fmax((double)v, -1.0), 1.0) : 0.0;
     s[a] += (long long)rint(c * KD_QSCALE);
@@ -199,58 +299,94 @@ __device__ __forceinline__ uint32_t longest_axis(const double *b) {
   return axis;
 }
 
-// Nodes of more than KD_WAVE_MAX photons take a whole workgroup; smaller ones
-// one wavefront each.
-constexpr uint32_t KD_WAVE_MAX = 2048;
+// Split test and median selection of node j, one workgroup.  Outputs per
+// node: sflag (1: splits, also counted in the node's chunk of ccnt), axis,
+// the split key and the number of photons below it.  tkey receives the node's
+// photon keys on the split axis (aligned with perm) for the partition.
+struct SelArgs {
+  const float *pos, *nrm;
+  const uint32_t *perm;
+  Level lv;
+  int split_allowed;  // the level lies above max_depth
+  double split_count, split_var;
+  uint32_t *tkey, *sflag, *sel, *ccnt;
+  uint32_t *err;
+  // First level, if the later ones are to read the photons in voxel order: what
+  // they will read.  The first level gathers photon i of the order from the
+  // caller's arrays (a line of memory each, 53 G lines/s) and leaves it here;
+  // the others find a node's photons within its voxel's few kilobytes.
+  float *pos_s, *nrm_s;
+};
+constexpr f32x3 NO3 = {0.0f, 0.0f, 0.0f};
 
-// Split test and median selection, one workgroup per node of a list (the
-// nodes above KD_WAVE_MAX photons; grid-stride over the list, whose length
-// the wavefront kernel wrote to *nbig).  Outputs per node: sflag (1: splits),
-// axis, the split key and the number of photons below it.  tkey receives the
-// node's photon keys on the split axis (aligned with perm) for the partition.
-__global__ __launch_bounds__(KD_THREADS) void kd_select_kernel(const float *__restrict__ pos,
-                                                               const float *__restrict__ nrm,
-                                                               const uint32_t *__restrict__ perm, Level lv,
-                                                               const uint32_t *__restrict__ big,
-                                                               const uint32_t *nbig, int depth, int max_depth,
-                                                               double split_count, double split_var,
-                                                               uint32_t *__restrict__ tkey,
-                                                               uint32_t *__restrict__ sflag,
-                                                               uint32_t *__restrict__ sel, uint32_t *err) {
-  __shared__ long long red[3][KD_THREADS / 64];
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t wsum[KD_THREADS / 64];
-  __shared__ uint32_t pick[2];
-  const uint32_t nb = *nbig;
-  for (uint32_t bi = blockIdx.x; bi < nb; bi += gridDim.x) {
-  __syncthreads();  // shared arrays of the previous node are no longer read
-  const uint32_t j = big[bi];
-  const uint32_t start = lv.start[j], M = lv.count[j];
-  bool split = false;
-  if (depth < max_depth && M >= 2) {
-    split = (double)M > split_count;
+__device__ __forceinline__ float axis_of(f32x3 p, uint32_t axis) { return axis == 0 ? p[0] : axis == 1 ? p[1] : p[2]; }
+// Nodes that share a counter of splits, and the distance of the counters in
+// words: atomics on one 128-byte line are done one after the other (10 ns
+// each: 18 counters side by side made 9000 splits take 80 us).
+constexpr int KD_CHUNK = 1024, KD_CSTEP = 32;
+
+__device__ __forceinline__ void put_selection(const SelArgs &a, uint32_t j, bool split, uint32_t axis, uint32_t key,
+                                              uint32_t less) {
+  a.sflag[j] = split ? 1u : 0u;
+  a.sel[3 * (size_t)j] = axis;
+  a.sel[3 * (size_t)j + 1] = key;
+  a.sel[3 * (size_t)j + 2] = less;
+  if (split) atomicAdd(&a.ccnt[(size_t)(j / KD_CHUNK) * KD_CSTEP], 1u);
+}
+
+__device__ __forceinline__ void select_group(const SelArgs &a, uint32_t j, uint32_t *hist,
+                                             long long (*red)[KD_BIG / 64], uint32_t *wsum, uint32_t *pick) {
+  const float *pos = a.pos, *nrm = a.nrm;
+  const uint32_t *perm = a.perm;
+  uint32_t *tkey = a.tkey;
+  const uint32_t start = a.lv.start[j], M = a.lv.count[j];
+  bool split = false, tested = false;
+  if (a.split_allowed && M >= 2) {
+    split = (double)M > a.split_count;
     if (!split && nrm) {
       long long s[3] = {0, 0, 0};
       bool bad = false;
-      for (uint32_t i = threadIdx.x; i < M; i += KD_THREADS) add_qnormal(nrm, perm[start + i], s, &bad);
-      if (bad) raise_err(err, ERR_RANGE);
+      for (uint32_t i = threadIdx.x; i < M; i += KD_BIG) {
+        const f32x3 v = load3(nrm, perm[start + i]);
+        if (a.nrm_s) store3(a.nrm_s, start + i, v);
+        add_qnormal(v, s, &bad);
+      }
+      tested = true;
+      if (bad) raise_err(a.err, ERR_RANGE);
       wg_sum3_i64(s, red);
-      split = variance_exceeds(s[0], s[1], s[2], M, split_var);
+      split = variance_exceeds(s[0], s[1], s[2], M, a.split_var);
     }
   }
   uint32_t axis = 0, key = 0, less = 0;
   if (split) {
-    axis = longest_axis(lv.box + 6 * (size_t)j);
+    axis = longest_axis(a.lv.box + 6 * (size_t)j);
+    const bool copy_n = a.nrm_s && !tested;
     // exact selection of the (M/2)-th smallest key, 8 bits per pass
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // keys of the split axis, and their range: bits above the highest one
     // where min and max differ are common to every key (and to the median)
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0;
-    for (uint32_t i = threadIdx.x; i < M; i += KD_THREADS) {
-      const uint32_t k = okey(pos[3 * (size_t)perm[start + i] + axis]);
-      tkey[start + i] = k;
-      kmin = min(kmin, k);
-      kmax = max(kmax, k);
+    for (uint32_t i0 = threadIdx.x; i0 < M; i0 += 4 * KD_BIG) {  // four keys in flight per lane
+      uint32_t ph[4];
+      f32x3 x[4] = {NO3, NO3, NO3, NO3}, v[4] = {NO3, NO3, NO3, NO3};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) ph[q] = i0 + q * KD_BIG < M ? perm[start + i0 + q * KD_BIG] : KD_NONE;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (ph[q] == KD_NONE) continue;
+        x[q] = load3(pos, ph[q]);
+        if (copy_n) v[q] = load3(nrm, ph[q]);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (ph[q] == KD_NONE) continue;
+        const uint32_t at = start + i0 + q * KD_BIG, k = okey(axis_of(x[q], axis));
+        tkey[at] = k;
+        if (a.pos_s) store3(a.pos_s, at, x[q]);
+        if (copy_n) store3(a.nrm_s, at, v[q]);
+        kmin = min(kmin, k);
+        kmax = max(kmax, k);
+      }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -263,7 +399,7 @@ __global__ __launch_bounds__(KD_THREADS) void kd_select_kernel(const float *__re
     }
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < KD_THREADS / 64; ++w) {
+    for (int w = 0; w < KD_BIG / 64; ++w) {
       kmin = min(kmin, wsum[w]);
       kmax = max(kmax, hist[w]);
     }
@@ -277,15 +413,19 @@ __global__ __launch_bounds__(KD_THREADS) void kd_select_kernel(const float *__re
     for (int hi = h; hi >= 0; hi -= 8) {
       const int sh = hi >= 7 ? hi - 7 : 0;
       const uint32_t dmask = (2u << (hi - sh)) - 1u;
-      hist[threadIdx.x] = 0;
+      if (threadIdx.x < 256) hist[threadIdx.x] = 0;
       __syncthreads();
-      for (uint32_t i = threadIdx.x; i < M; i += KD_THREADS) {
-        const uint32_t k = tkey[start + i];
-        if (((k ^ prefix) & pmask) == 0) atomicAdd(&hist[(k >> sh) & dmask], 1u);
+      for (uint32_t i0 = threadIdx.x; i0 < M; i0 += 4 * KD_BIG) {
+        uint32_t k[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) k[q] = i0 + q * KD_BIG < M ? tkey[start + i0 + q * KD_BIG] : 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (i0 + q * KD_BIG < M && ((k[q] ^ prefix) & pmask) == 0) atomicAdd(&hist[(k[q] >> sh) & dmask], 1u);
       }
       __syncthreads();
-      // inclusive scan of the 256 digit counts (one per thread)
-      const uint32_t c = hist[threadIdx.x];
+      // inclusive scan of the 256 digit counts (one per thread, the rest idle)
+      const uint32_t c = threadIdx.x < 256 ? hist[threadIdx.x] : 0u;
       uint32_t inc = c;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
@@ -294,7 +434,7 @@ __global__ __launch_bounds__(KD_THREADS) void kd_select_kernel(const float *__re
       }
       if (lane == 63) wsum[wave] = inc;
       __syncthreads();
-      for (int w = 0; w < wave; ++w) inc += wsum[w];
+      for (int w = 0; w < wave && w < 4; ++w) inc += wsum[w];
       const uint32_t exc = inc - c;
       if (exc <= m && m < inc) {  // exactly one digit holds rank m
         pick[0] = threadIdx.x;
@@ -311,13 +451,7 @@ __global__ __launch_bounds__(KD_THREADS) void kd_select_kernel(const float *__re
     key = prefix;  // all keys equal (h < 0): the common key, nothing below it
     split = less > 0;
   }
-  if (threadIdx.x == 0) {
-    sflag[j] = split ? 1u : 0u;
-    sel[3 * (size_t)j] = axis;
-    sel[3 * (size_t)j + 1] = key;
-    sel[3 * (size_t)j + 2] = less;
-  }
-  }
+  if (threadIdx.x == 0) put_selection(a, j, split, axis, key, less);
 }
 
 // Orders this wavefront's LDS accesses before and after it (the lanes of a
@@ -328,28 +462,113 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The same split test and selection with one wavefront per node (four nodes
-// per workgroup) for nodes of at most KD_WAVE_MAX photons; a larger node is
-// appended to the list `big` for kd_select_kernel.  Each wavefront works
-// alone (its own LDS histogram, no workgroup barrier).
-__global__ __launch_bounds__(KD_THREADS) void kd_select_wave_kernel(
-    const float *__restrict__ pos, const float *__restrict__ nrm, const uint32_t *__restrict__ perm, Level lv,
-    uint32_t active, int depth, int max_depth, double split_count, double split_var, uint32_t *__restrict__ tkey,
-    uint32_t *__restrict__ sflag, uint32_t *__restrict__ sel, uint32_t *__restrict__ big, uint32_t *nbig,
-    uint32_t *err) {
-  __shared__ uint32_t hist_all[KD_THREADS / 64][256];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t j = blockIdx.x * (KD_THREADS / 64) + wave;
-  if (j >= active) return;
-  const uint32_t start = lv.start[j], M = lv.count[j];
-  if (M > KD_WAVE_MAX) {
-    if (lane == 0) big[atomicAdd(nbig, 1u)] = j;
-    return;
+// The same with one wavefront for a node of at most REG_MAX photons, its keys in
+// registers: the bits of the median from the highest differing one down, each
+// from the ballots of the keys that still match (no LDS, no second read of
+// the keys; deep levels hold hundreds of thousands of nodes of a few dozen
+// photons.  In 4 x 64 registers the bits cost more than the histograms).
+constexpr uint32_t REG_MAX = 128;
+template <int Q>
+__device__ __forceinline__ void select_regs(const SelArgs &a, uint32_t j, uint32_t start, uint32_t M) {
+  static_assert(64 * Q <= 1024, "the sums of quantised normals fit 32 bits");
+  const int lane = threadIdx.x & 63;
+  uint32_t ph[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) ph[q] = 64 * q + lane < M ? a.perm[start + 64 * q + lane] : KD_NONE;
+  bool split = false, tested = false;
+  if (a.split_allowed && M >= 2) {
+    split = (double)M > a.split_count;
+    if (!split && a.nrm) {
+      long long s64[3] = {0, 0, 0};
+      bool bad = false;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        if (ph[q] == KD_NONE) continue;
+        const f32x3 v = load3(a.nrm, ph[q]);
+        if (a.nrm_s) store3(a.nrm_s, start + 64 * q + lane, v);
+        add_qnormal(v, s64, &bad);
+      }
+      tested = true;
+      if (bad) raise_err(a.err, ERR_RANGE);
+      int s[3] = {(int)s64[0], (int)s64[1], (int)s64[2]};
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s[c] += __shfl_xor(s[c], o);
+      split = variance_exceeds(s[0], s[1], s[2], M, a.split_var);
+    }
   }
-  uint32_t *hist = hist_all[wave];
-  bool split = false;
-  if (depth < max_depth && M >= 2) {
-    split = (double)M > split_count;
+  uint32_t axis = 0, key = 0, less = 0;
+  if (split) {
+    axis = longest_axis(a.lv.box + 6 * (size_t)j);
+    const bool copy_n = a.nrm_s && !tested;
+    float x[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      x[q] = 0.0f;
+      if (ph[q] == KD_NONE) continue;
+      const f32x3 p = load3(a.pos, ph[q]);
+      x[q] = axis_of(p, axis);
+      if (a.pos_s) store3(a.pos_s, start + 64 * q + lane, p);
+      if (copy_n) store3(a.nrm_s, start + 64 * q + lane, load3(a.nrm, ph[q]));
+    }
+    uint32_t k[Q], kmin = 0xFFFFFFFFu, kmax = 0;
+    uint64_t cand[Q];  // keys that agree with the median so far
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      k[q] = okey(x[q]);
+      cand[q] = __ballot(ph[q] != KD_NONE);
+      if (ph[q] == KD_NONE) continue;
+      a.tkey[start + 64 * q + lane] = k[q];
+      kmin = min(kmin, k[q]);
+      kmax = max(kmax, k[q]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      kmin = min(kmin, (uint32_t)__shfl_xor(kmin, o));
+      kmax = max(kmax, (uint32_t)__shfl_xor(kmax, o));
+    }
+    kmin = __builtin_amdgcn_readfirstlane(kmin);
+    kmax = __builtin_amdgcn_readfirstlane(kmax);
+    uint32_t m = M / 2;
+    const int h = kmin == kmax ? -1 : 31 - __clz(kmin ^ kmax);
+    key = h < 0 ? kmin : (h >= 31 ? 0u : kmin & ~((2u << h) - 1u));
+    for (int b = h; b >= 0; --b) {
+      uint64_t z[Q];
+      uint32_t c = 0;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        z[q] = cand[q] & ~__ballot((k[q] >> b) & 1u);
+        c += (uint32_t)__popcll(z[q]);
+      }
+      const bool low = m < c;
+      if (!low) {
+        m -= c;
+        less += c;
+        key |= 1u << b;
+      }
+#pragma unroll
+      for (int q = 0; q < Q; ++q) cand[q] = low ? z[q] : cand[q] & ~z[q];
+    }
+    split = less > 0;
+  }
+  if (lane == 0) put_selection(a, j, split, axis, key, less);
+}
+
+// The same with one wavefront for a node of at most KD_WAVE_MAX photons; it
+// works alone (its own LDS histogram, no workgroup barrier).
+__device__ __forceinline__ void select_wave(const SelArgs &a, uint32_t j, uint32_t *hist) {
+  const float *pos = a.pos, *nrm = a.nrm;
+  const uint32_t *perm = a.perm;
+  uint32_t *tkey = a.tkey;
+  const int lane = threadIdx.x & 63;
+  const uint32_t start = a.lv.start[j], M = a.lv.count[j];
+  if (M > KD_WAVE_MAX) return;
+  if (M <= 64) return select_regs<1>(a, j, start, M);
+  if (M <= REG_MAX) return select_regs<REG_MAX / 64>(a, j, start, M);
+  bool split = false, tested = false;
+  if (a.split_allowed && M >= 2) {
+    split = (double)M > a.split_count;
     if (!split && nrm) {
       long long s[3] = {0, 0, 0};
       bool bad = false;
@@ -361,24 +580,31 @@ __global__ __launch_bounds__(KD_THREADS) void kd_select_wave_kernel(
           ph[q] = i < M ? perm[start + i] : KD_NONE;
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (ph[q] != KD_NONE) add_qnormal(nrm, ph[q], s, &bad);
+        for (int q = 0; q < 4; ++q) {
+          if (ph[q] == KD_NONE) continue;
+          const f32x3 v = load3(nrm, ph[q]);
+          if (a.nrm_s) store3(a.nrm_s, start + i0 + 64 * q + lane, v);
+          add_qnormal(v, s, &bad);
+        }
       }
-      if (bad) raise_err(err, ERR_RANGE);
+      tested = true;
+      if (bad) raise_err(a.err, ERR_RANGE);
 #pragma unroll
-      for (int a = 0; a < 3; ++a)
+      for (int c = 0; c < 3; ++c)
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) s[a] += __shfl_xor(s[a], o);
-      split = variance_exceeds(s[0], s[1], s[2], M, split_var);
+        for (int o = 32; o > 0; o >>= 1) s[c] += __shfl_xor(s[c], o);
+      split = variance_exceeds(s[0], s[1], s[2], M, a.split_var);
     }
   }
   uint32_t axis = 0, key = 0, less = 0;
   if (split) {
-    axis = longest_axis(lv.box + 6 * (size_t)j);
+    axis = longest_axis(a.lv.box + 6 * (size_t)j);
+    const bool copy_n = a.nrm_s && !tested;
     // keys of the split axis and their range (as in kd_select_kernel)
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0;
     for (uint32_t i0 = 0; i0 < M; i0 += 4 * 64) {  // four keys in flight per lane
       uint32_t ph[4];
+      f32x3 x[4] = {NO3, NO3, NO3, NO3}, v[4] = {NO3, NO3, NO3, NO3};
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const uint32_t i = i0 + 64 * q + lane;
@@ -387,8 +613,16 @@ __global__ __launch_bounds__(KD_THREADS) void kd_select_wave_kernel(
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         if (ph[q] == KD_NONE) continue;
-        const uint32_t k = okey(pos[3 * (size_t)ph[q] + axis]);
-        tkey[start + i0 + 64 * q + lane] = k;
+        x[q] = load3(pos, ph[q]);
+        if (copy_n) v[q] = load3(nrm, ph[q]);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (ph[q] == KD_NONE) continue;
+        const uint32_t at = start + i0 + 64 * q + lane, k = okey(axis_of(x[q], axis));
+        tkey[at] = k;
+        if (a.pos_s) store3(a.pos_s, at, x[q]);
+        if (copy_n) store3(a.nrm_s, at, v[q]);
         kmin = min(kmin, k);
         kmax = max(kmax, k);
       }
@@ -459,112 +693,330 @@ __global__ __launch_bounds__(KD_THREADS) void kd_select_wave_kernel(
     key = prefix;  // all keys equal (h < 0): the common key, nothing below it
     split = less > 0;
   }
-  if (lane == 0) {
-    sflag[j] = split ? 1u : 0u;
-    sel[3 * (size_t)j] = axis;
-    sel[3 * (size_t)j + 1] = key;
-    sel[3 * (size_t)j + 2] = less;
+  if (lane == 0) put_selection(a, j, split, axis, key, less);
+}
+
+// One level's selections: the nodes of `big`, a workgroup of 1024 each, and
+// the small ones.  A level lasts as long as its largest node, whose photons go
+// through one workgroup: with 256 threads the levels of 20 million photons
+// with one voxel of 170 thousand took 200 us each, whatever the others held.
+__global__ __launch_bounds__(KD_BIG) void kd_select_big_kernel(SelArgs a, const LevelState *ls,
+                                                               const uint32_t *__restrict__ big) {
+  __shared__ uint32_t hist[256];
+  __shared__ long long red[3][KD_BIG / 64];
+  __shared__ uint32_t wsum[KD_BIG / 64];
+  __shared__ uint32_t pick[2];
+  const uint32_t nb = ls->nbig;
+  for (uint32_t bi = blockIdx.x; bi < nb; bi += gridDim.x) {
+    __syncthreads();  // shared arrays of the previous node are no longer read
+    select_group(a, big[bi], hist, red, wsum, pick);
   }
 }
 
-// After the scan of the split flags: the list of splitting nodes, and the
-// leaf record of every other node (slot leaf_base + number of non-splitting
-// nodes before it).
-__global__ __launch_bounds__(256) void kd_lists_kernel(Level lv, uint32_t active, const uint32_t *__restrict__ sflag,
-                                                       const uint32_t *__restrict__ srank,
+__global__ __launch_bounds__(KD_THREADS) void kd_select_kernel(SelArgs a, const LevelState *ls) {
+  __shared__ uint32_t hist[KD_THREADS / 64][256];
+  const uint32_t active = ls->active, wave = threadIdx.x >> 6;
+  for (uint32_t j = blockIdx.x * (KD_THREADS / 64) + wave; j < active; j += gridDim.x * (KD_THREADS / 64)) {
+    wave_sync();
+    select_wave(a, j, hist[wave]);
+  }
+}
+
+// From the split flags of a level: the list of splitting nodes, the leaf
+// record of every other node (slot leaf_base + number of non-splitting nodes
+// before it) with the bit of its segment start, and the next level's state.
+// Every workgroup takes a range of chunks and sums the counters before it.
+__global__ __launch_bounds__(256) void kd_lists_kernel(Level lv, BuildState *st, int depth, uint32_t cap,
+                                                       uint32_t *__restrict__ sflag,
+                                                       const uint32_t *__restrict__ ccnt,
+                                                       uint32_t *__restrict__ ccnt_next,
                                                        uint32_t *__restrict__ split_list,
                                                        uint32_t *__restrict__ leaf_start,
-                                                       uint32_t *__restrict__ leaf_node, uint32_t leaf_base) {
-  const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= active) return;
-  if (sflag[j]) {
-    split_list[srank[j]] = j;
-  } else {
-    const uint32_t slot = leaf_base + (j - srank[j]);
-    leaf_start[slot] = lv.start[j];
-    leaf_node[slot] = lv.id[j];
+                                                       uint32_t *__restrict__ leaf_node,
+                                                       uint32_t *__restrict__ leaf_bits) {
+  __shared__ uint32_t wa[4], wb[4];
+  const LevelState cur = st->lv[depth];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // the counters of the next level were last used one level ago
+  const uint32_t old = depth ? (st->lv[depth - 1].active + KD_CHUNK - 1) / KD_CHUNK : 0;
+  for (uint32_t c = blockIdx.x * 256 + threadIdx.x; c < old; c += gridDim.x * 256) ccnt_next[(size_t)c * KD_CSTEP] = 0;
+  const uint32_t chunks = (cur.active + KD_CHUNK - 1) / KD_CHUNK;
+  const uint32_t per = (chunks + gridDim.x - 1) / gridDim.x;
+  const uint32_t c0 = min(chunks, blockIdx.x * per), c1 = min(chunks, c0 + per);
+  if (c0 == c1 && blockIdx.x) return;
+  uint32_t before = 0, total = 0;
+  for (uint32_t c = threadIdx.x; c < chunks; c += 256) {
+    const uint32_t v = ccnt[(size_t)c * KD_CSTEP];
+    total += v;
+    if (c < c0) before += v;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    before += __shfl_xor(before, o);
+    total += __shfl_xor(total, o);
+  }
+  if (lane == 0) {
+    wa[wave] = before;
+    wb[wave] = total;
+  }
+  __syncthreads();
+  before = wa[0] + wa[1] + wa[2] + wa[3];
+  total = wb[0] + wb[1] + wb[2] + wb[3];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    // leaves so far + this level's + at least one per child: the bound keeps
+    // the next level's records and every leaf slot within max_leaves
+    const uint32_t emitted = cur.leaf_base + (cur.active - total);
+    const bool fits = (uint64_t)emitted + 2ull * total <= cap;
+    if (!fits) st->over = 1;
+    st->lv[depth].nsplit = fits ? total : 0;
+    st->lv[depth + 1].active = fits ? 2 * total : 0;
+    st->lv[depth + 1].leaf_base = emitted;
+    st->lv[depth + 1].nodes = cur.nodes + 2 * total;
+  }
+  for (uint32_t c = c0; c < c1; ++c) {
+    const uint32_t j0 = c * KD_CHUNK + 4 * threadIdx.x;
+    uint32_t f[4], sum = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      f[q] = j0 + q < cur.active ? sflag[j0 + q] : 0u;
+      sum += f[q];
+    }
+    uint32_t inc = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t t = __shfl_up(inc, o);
+      if (lane >= o) inc += t;
+    }
+    __syncthreads();
+    if (lane == 63) wa[wave] = inc;
+    __syncthreads();
+    uint32_t r = before + inc - sum;
+    for (int w = 0; w < wave; ++w) r += wa[w];
+    before += wa[0] + wa[1] + wa[2] + wa[3];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t j = j0 + q;
+      if (j >= cur.active) continue;
+      if (f[q]) {
+        split_list[r] = j;
+        sflag[j] = ++r;  // its place in the list, plus one
+      } else {
+        const uint32_t slot = cur.leaf_base + (j - r), s0 = lv.start[j];
+        leaf_start[slot] = s0;
+        leaf_node[slot] = lv.id[j];
+        atomicOr(&leaf_bits[s0 >> 5], 1u << (s0 & 31));
+      }
+    }
   }
 }
 
-// Partition of the splitting nodes, one workgroup per node of split_list:
-// the segment is partitioned stably into tmp and copied back in place; the
-// node's record and its two children are written.
-__global__ __launch_bounds__(KD_THREADS) void kd_partition_kernel(
-    uint32_t *__restrict__ perm, uint32_t *__restrict__ tmp, const uint32_t *__restrict__ tkey, Level lv, Level nx,
-    const uint32_t *__restrict__ split_list, const uint32_t *__restrict__ srank, const uint32_t *__restrict__ sel,
-    uint32_t node_base_next, npg_kd_node *__restrict__ nodes) {
-  __shared__ uint32_t wl[KD_THREADS / 64], wr[KD_THREADS / 64];
-  const uint32_t j = split_list[blockIdx.x];
-  const uint32_t start = lv.start[j], M = lv.count[j], id = lv.id[j];
-  const uint32_t axis = sel[3 * (size_t)j], key = sel[3 * (size_t)j + 1], less = sel[3 * (size_t)j + 2];
-  const uint32_t c0 = node_base_next + 2 * srank[j];
+// What a partition writes besides the photons: the node's record and its two
+// children, nodes 2k and 2k + 1 of the next level (k: place in the split list).
+__device__ __forceinline__ void put_children(Level lv, Level nx, uint32_t j, uint32_t k, uint32_t base, uint32_t axis,
+                                             uint32_t key, uint32_t less, LevelState *next, uint32_t *big,
+                                             npg_kd_node *nodes) {
+  const uint32_t start = lv.start[j], M = lv.count[j], id = lv.id[j], c0 = base + 2 * k, q0 = 2 * k;
+  const float s = okey_inv(key);
+  nodes[id].split = s;
+  nodes[id].info = (c0 << 2) | axis;
+  nx.start[q0] = start;
+  nx.count[q0] = less;
+  nx.id[q0] = c0;
+  nx.start[q0 + 1] = start + less;
+  nx.count[q0 + 1] = M - less;
+  nx.id[q0 + 1] = c0 + 1;
+  note_big(less, q0, next, big);
+  note_big(M - less, q0 + 1, next, big);
+  const double *b = lv.box + 6 * (size_t)j;
+  double *bl0 = nx.box + 6 * (size_t)q0, *br0 = nx.box + 6 * (size_t)(q0 + 1);
+  for (int q = 0; q < 6; ++q) {
+    bl0[q] = b[q];
+    br0[q] = b[q];
+  }
+  bl0[3 + axis] = (double)s;
+  br0[axis] = (double)s;
+}
+
+// Stable partition of one node's segment by one workgroup of NT threads, in
+// rounds of PART_G * NT photons, through tmp: a photon's slot follows from the
+// number of left photons before it.
+constexpr int PART_G = 8;
+template <int NT>
+__device__ __forceinline__ void partition_node(uint32_t *__restrict__ perm, uint32_t *__restrict__ tmp,
+                                               const uint32_t *__restrict__ tkey, uint32_t start, uint32_t M,
+                                               uint32_t key, uint32_t less, uint32_t *wl) {
+  constexpr uint32_t ROUND = PART_G * NT;
+  constexpr int NW = NT / 64, PER = (PART_G * NW + 63) / 64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-  uint32_t lbase = 0, rbase = 0;
-  for (uint32_t r0 = 0; r0 < M; r0 += KD_THREADS) {
-    const uint32_t i = r0 + threadIdx.x;
-    const bool act = i < M;
-    const bool left = act && tkey[start + i] < key;
-    const uint64_t bl = __ballot(left), br = __ballot(act && !left);
-    if (lane == 0) {
-      wl[wave] = (uint32_t)__popcll(bl);
-      wr[wave] = (uint32_t)__popcll(br);
+  uint32_t lbase = 0;  // left photons of the rounds before
+  for (uint32_t r0 = 0; r0 < M; r0 += ROUND) {
+    const int groups = (int)((min(M - r0, ROUND) + NT - 1) / NT);
+    uint32_t ph[PART_G], tk[PART_G];
+    uint64_t bl[PART_G];
+#pragma unroll
+    for (int g = 0; g < PART_G; ++g)
+      if (g < groups) {
+        const uint32_t i = r0 + g * NT + threadIdx.x;
+        tk[g] = i < M ? tkey[start + i] : 0xFFFFFFFFu;
+        ph[g] = i < M ? perm[start + i] : 0u;
+      }
+#pragma unroll
+    for (int g = 0; g < PART_G; ++g) {
+      const uint32_t i = r0 + g * NT + threadIdx.x;
+      bl[g] = g < groups ? __ballot(i < M && tk[g] < key) : 0ull;
+      if (lane == 0) wl[g * NW + wave] = (uint32_t)__popcll(bl[g]);
     }
     __syncthreads();
-    uint32_t ol = lbase, orr = rbase, tl = 0, tr = 0;
+    if (wave == 0) {  // left photons before each group of 64, and in all of them
+      uint32_t c[PER], sum = 0;
 #pragma unroll
-    for (int w = 0; w < KD_THREADS / 64; ++w) {
-      if (w < wave) {
-        ol += wl[w];
-        orr += wr[w];
+      for (int q = 0; q < PER; ++q) {
+        const int w = PER * lane + q;
+        c[q] = w < PART_G * NW ? wl[w] : 0u;
+        sum += c[q];
       }
-      tl += wl[w];
-      tr += wr[w];
+      uint32_t inc = sum;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(inc, o);
+        if (lane >= o) inc += t;
+      }
+      uint32_t exc = inc - sum;
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        const int w = PER * lane + q;
+        if (w < PART_G * NW) wl[w] = exc;
+        exc += c[q];
+      }
+      if (lane == 63) wl[PART_G * NW] = inc;
     }
-    if (act) {
-      const uint32_t dst = left ? start + ol + (uint32_t)__popcll(bl & below)
-                                : start + less + orr + (uint32_t)__popcll(br & below);
-      tmp[dst] = perm[start + i];
-    }
-    lbase += tl;
-    rbase += tr;
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < PART_G; ++g)
+      if (g < groups) {
+        const uint32_t i = r0 + g * NT + threadIdx.x;
+        const uint32_t l = lbase + wl[g * NW + wave] + (uint32_t)__popcll(bl[g] & below);
+        if (i < M) {
+          const uint32_t dst = tk[g] < key ? l : less + (i - l);
+          tmp[start + dst] = ph[g];
+        }
+      }
+    lbase += wl[PART_G * NW];
     __syncthreads();
   }
-  // every read of the segment is done (barrier above): copy back in place
-  for (uint32_t i = threadIdx.x; i < M; i += KD_THREADS) perm[start + i] = tmp[start + i];
-  if (threadIdx.x == 0) {
-    const float s = okey_inv(key);
-    nodes[id].split = s;
-    nodes[id].info = (c0 << 2) | axis;
-    const uint32_t q0 = 2 * srank[j];
-    nx.start[q0] = start;
-    nx.count[q0] = less;
-    nx.id[q0] = c0;
-    nx.start[q0 + 1] = start + less;
-    nx.count[q0 + 1] = M - less;
-    nx.id[q0 + 1] = c0 + 1;
-    const double *b = lv.box + 6 * (size_t)j;
-    double *bl0 = nx.box + 6 * (size_t)q0, *br0 = nx.box + 6 * (size_t)(q0 + 1);
-    for (int k = 0; k < 6; ++k) {
-      bl0[k] = b[k];
-      br0[k] = b[k];
-    }
-    bl0[3 + axis] = (double)s;
-    br0[axis] = (double)s;
+  // every read of the segment is done (barrier above): write it in place
+  for (uint32_t i = threadIdx.x; i < M; i += NT) perm[start + i] = tmp[start + i];
+  __syncthreads();  // wl is free for the next node
+}
+
+// The same by one wavefront for a node of at most KD_WAVE_MAX photons: one
+// round is kept in registers and written straight to its places, more go
+// through buf (LDS).
+__device__ __forceinline__ void partition_wave(uint32_t *__restrict__ perm, const uint32_t *__restrict__ tkey,
+                                               uint32_t start, uint32_t M, uint32_t key, uint32_t less,
+                                               uint32_t *buf) {
+  constexpr uint32_t ROUND = PART_G * 64;
+  const int lane = threadIdx.x & 63;
+  const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
+  const bool one = M <= ROUND;
+  uint32_t lbase = 0;
+  for (uint32_t r0 = 0; r0 < M; r0 += ROUND) {
+    const int groups = (int)((min(M - r0, ROUND) + 63) / 64);
+    uint32_t ph[PART_G], tk[PART_G];
+#pragma unroll
+    for (int g = 0; g < PART_G; ++g)
+      if (g < groups) {
+        const uint32_t i = r0 + g * 64 + lane;
+        tk[g] = i < M ? tkey[start + i] : 0xFFFFFFFFu;
+        ph[g] = i < M ? perm[start + i] : 0u;
+      }
+    // the photons are read before any is written
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int g = 0; g < PART_G; ++g)
+      if (g < groups) {
+        const uint32_t i = r0 + g * 64 + lane;
+        const uint64_t bl = __ballot(i < M && tk[g] < key);
+        const uint32_t l = lbase + (uint32_t)__popcll(bl & below);
+        lbase += (uint32_t)__popcll(bl);
+        if (i < M) {
+          const uint32_t dst = tk[g] < key ? l : less + (i - l);
+          if (one)
+            perm[start + dst] = ph[g];
+          else
+            buf[dst] = ph[g];
+        }
+      }
+  }
+  if (one) return;
+  wave_sync();
+  for (uint32_t i = lane; i < M; i += 64) perm[start + i] = buf[i];
+  wave_sync();  // buf is free for the next node
+}
+
+// Partitions of a level: the nodes of the split list of at most KD_WAVE_MAX
+// photons, one wavefront each (a workgroup each took 250 us a level where
+// hundreds of thousands of nodes hold a few dozen photons), and those of `big`
+// that split (sflag: place in the split list plus one).  big_next receives the
+// large children.
+__global__ __launch_bounds__(KD_THREADS) void kd_partition_kernel(
+    uint32_t *__restrict__ perm, const uint32_t *__restrict__ tkey, Level lv, Level nx,
+    const uint32_t *__restrict__ split_list, const uint32_t *__restrict__ sel, BuildState *st, int depth,
+    uint32_t *__restrict__ big_next, npg_kd_node *__restrict__ nodes) {
+  __shared__ uint32_t buf[KD_THREADS / 64][KD_WAVE_MAX];
+  const uint32_t nsplit = st->lv[depth].nsplit, base = st->lv[depth].nodes, wave = threadIdx.x >> 6;
+  for (uint32_t k = blockIdx.x * (KD_THREADS / 64) + wave; k < nsplit; k += gridDim.x * (KD_THREADS / 64)) {
+    const uint32_t j = split_list[k], M = lv.count[j];
+    if (M > KD_WAVE_MAX) continue;
+    const uint32_t axis = sel[3 * (size_t)j], key = sel[3 * (size_t)j + 1], less = sel[3 * (size_t)j + 2];
+    if ((threadIdx.x & 63) == 0)
+      put_children(lv, nx, j, k, base, axis, key, less, &st->lv[depth + 1], big_next, nodes);
+    partition_wave(perm, tkey, lv.start[j], M, key, less, buf[wave]);
   }
 }
 
-__global__ __launch_bounds__(256) void kd_leaves_kernel(const uint32_t *__restrict__ start_sorted,
-                                                        const uint32_t *__restrict__ node_sorted, uint32_t L,
-                                                        const uint32_t *nvalid, uint32_t *__restrict__ leaf_off,
-                                                        npg_kd_node *__restrict__ nodes) {
-  const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < L) {
-    leaf_off[k] = start_sorted[k];
-    nodes[node_sorted[k]].split = 0.0f;
-    nodes[node_sorted[k]].info = (k << 2) | 3u;
+__global__ __launch_bounds__(KD_BIG) void kd_partition_big_kernel(
+    uint32_t *__restrict__ perm, uint32_t *__restrict__ tmp, const uint32_t *__restrict__ tkey, Level lv, Level nx,
+    const uint32_t *__restrict__ big, const uint32_t *__restrict__ sflag, const uint32_t *__restrict__ sel,
+    BuildState *st, int depth, uint32_t *__restrict__ big_next, npg_kd_node *__restrict__ nodes) {
+  __shared__ uint32_t wl[PART_G * KD_BIG / 64 + 1];
+  const uint32_t nb = st->lv[depth].nsplit ? st->lv[depth].nbig : 0, base = st->lv[depth].nodes;
+  for (uint32_t bi = blockIdx.x; bi < nb; bi += gridDim.x) {
+    const uint32_t j = big[bi], k1 = sflag[j];
+    if (!k1) continue;
+    const uint32_t axis = sel[3 * (size_t)j], key = sel[3 * (size_t)j + 1], less = sel[3 * (size_t)j + 2];
+    if (threadIdx.x == 0) put_children(lv, nx, j, k1 - 1, base, axis, key, less, &st->lv[depth + 1], big_next, nodes);
+    partition_node<KD_BIG>(perm, tmp, tkey, lv.start[j], lv.count[j], key, less, wl);
   }
-  if (k == 0) leaf_off[L] = *nvalid;
+}
+
+__global__ __launch_bounds__(256) void kd_popc_kernel(const uint32_t *__restrict__ bits, uint64_t nw,
+                                                      uint32_t *__restrict__ cnt) {
+  for (uint64_t w = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; w < nw; w += (uint64_t)gridDim.x * blockDim.x)
+    cnt[w] = (uint32_t)__popc(bits[w]);
+}
+
+// leaf k = k-th leaf start in ascending order (starts are distinct: no node
+// is empty)
+__global__ __launch_bounds__(256) void kd_leaves_kernel(const uint32_t *__restrict__ leaf_start,
+                                                        const uint32_t *__restrict__ leaf_node,
+                                                        const uint32_t *__restrict__ bits,
+                                                        const uint32_t *__restrict__ rank, int last,
+                                                        BuildState *st, uint32_t *__restrict__ leaf_off,
+                                                        npg_kd_node *__restrict__ nodes, const uint32_t *err) {
+  const uint32_t t0 = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t0 == 0) st->err = *err;
+  if (st->over) return;
+  const uint32_t L = st->lv[last].leaf_base;
+  for (uint32_t q = t0; q < L; q += gridDim.x * blockDim.x) {
+    const uint32_t s0 = leaf_start[q], w = s0 >> 5;
+    const uint32_t k = rank[w] + (uint32_t)__popc(bits[w] & ((1u << (s0 & 31)) - 1u));
+    leaf_off[k] = s0;
+    nodes[leaf_node[q]].split = 0.0f;
+    nodes[leaf_node[q]].info = (k << 2) | 3u;
+  }
+  if (t0 == 0) leaf_off[L] = st->nvalid;
 }
 
 __global__ __launch_bounds__(256) void kd_locate_kernel(GridDev g, const int32_t *__restrict__ root,
@@ -620,12 +1072,15 @@ int grid_params(npg_ctx *ctx, const npg_kdgrid_params *p, GridDev *g) {
   return NPG_OK;
 }
 
-int take_err(npg_ctx *ctx, hipStream_t s, uint32_t *errw) {
-  NPG_HIP_CHECK(ctx, hipMemcpyAsync(errw, ctx->err_dev, 4, hipMemcpyDeviceToHost, s));
-  NPG_HIP_CHECK(ctx, hipStreamSynchronize(s));
-  if (*errw) NPG_HIP_CHECK(ctx, hipMemsetAsync(ctx->err_dev, 0, 4, s));
-  return NPG_OK;
-}
+// Workgroups of a level's kernels, which stride over the nodes there are: more
+// than fit the chip at once (2048), so that nodes of unequal size even out,
+// and few enough that a level without nodes costs 5 us.
+constexpr uint64_t KD_GRID = 8192;
+
+// Most photons whose positions and normals are copied into voxel order (24
+// bytes each: 6.4 GB).  Beyond, and for trees of one level, which read each
+// photon once anyway, every level gathers from the caller's arrays.
+constexpr uint64_t VOXEL_ORDER_MAX = 1ull << 28;
 
 }  // namespace
 
@@ -672,22 +1127,27 @@ extern "C" int npg_build_kdgrid(npg_ctx *ctx, const npg_kdgrid_params *params, c
   const uint64_t m = n ? n : 1;
   const uint64_t cap = max_leaves;
   // scratch
-  const size_t sort_work = npg_radix_work_bytes(std::max<uint64_t>(m, cap));
-  size_t bytes = 5 * npg_align(4 * m) + npg_align(4 * (m + 1)) + sort_work;
-  bytes += npg_align(4 * npg_scan_tmp_words(std::max<uint64_t>(m, cap)));
-  bytes += 2 * (3 * npg_align(4 * cap) + npg_align(48 * cap));   // two levels
-  bytes += 2 * npg_align(4 * (cap + 1)) + npg_align(12 * cap) + npg_align(4 * cap);  // sflag, srank, sel, lists
-  bytes += 4 * npg_align(4 * cap) + npg_align(16);               // leaves, sorted leaves, counters
+  const uint64_t nw = (m + 31) / 32;         // words of a bitmap over the photons
+  const uint64_t nch = (cap / KD_CHUNK + 1) * KD_CSTEP;  // split counters of a level
+  const size_t sort_work = npg_radix_work_bytes(m);
+  const bool voxel_order = params->max_depth >= 2 && n <= VOXEL_ORDER_MAX;
+  size_t bytes = 4 * npg_align(4 * m) + sort_work;
+  bytes += 3 * npg_align(4 * (nw + 1)) + npg_align(4 * npg_scan_tmp_words(nw));
+  bytes += 2 * (3 * npg_align(4 * cap) + npg_align(48 * cap));        // two levels
+  bytes += 2 * npg_align(4 * cap) + npg_align(12 * cap);              // sflag, split list, sel
+  bytes += 2 * npg_align(4 * cap) + 2 * npg_align(4 * nch);           // leaves, split counters
+  bytes += 2 * npg_align(4 * (m / KD_WAVE_MAX + 1)) + npg_align(sizeof(BuildState));
+  if (voxel_order) bytes += npg_align(4 * m) + (normal_dev ? 2 : 1) * npg_align(12 * m);
   void *scr = nullptr;
   rc = npg_scratch(ctx, bytes, s, &scr);
   if (rc) return rc;
   Carver cv(scr);
   uint32_t *key = cv.take<uint32_t>(m), *ks = cv.take<uint32_t>(m);
   uint32_t *pa = cv.take<uint32_t>(m);  // partition staging
-  uint32_t *tkey = cv.take<uint32_t>(m), *flag = cv.take<uint32_t>(m);
-  uint32_t *seg = cv.take<uint32_t>(m + 1);
+  uint32_t *tkey = cv.take<uint32_t>(m);
   void *work = cv.take<char>(sort_work);
-  uint32_t *stmp = cv.take<uint32_t>(npg_scan_tmp_words(std::max<uint64_t>(m, cap)));
+  uint32_t *bits = cv.take<uint32_t>(nw + 1), *cnt = cv.take<uint32_t>(nw + 1), *rank = cv.take<uint32_t>(nw + 1);
+  uint32_t *stmp = cv.take<uint32_t>(npg_scan_tmp_words(nw));
   Level lv[2];
   for (auto &l : lv) {
     l.start = cv.take<uint32_t>(cap);
@@ -695,93 +1155,90 @@ extern "C" int npg_build_kdgrid(npg_ctx *ctx, const npg_kdgrid_params *params, c
     l.id = cv.take<uint32_t>(cap);
     l.box = cv.take<double>(6 * cap);
   }
-  uint32_t *sflag = cv.take<uint32_t>(cap + 1), *srank = cv.take<uint32_t>(cap + 1);
+  uint32_t *sflag = cv.take<uint32_t>(cap), *slist = cv.take<uint32_t>(cap);
   uint32_t *sel = cv.take<uint32_t>(3 * cap);
-  uint32_t *big = cv.take<uint32_t>(cap);  // big-node list, then the split list
   uint32_t *lstart = cv.take<uint32_t>(cap), *lnode = cv.take<uint32_t>(cap);
-  uint32_t *lstart_s = cv.take<uint32_t>(cap), *lnode_s = cv.take<uint32_t>(cap);
-  uint32_t *ctr = cv.take<uint32_t>(4);  // [0] photons in valid voxels, [1] big nodes of a level
+  uint32_t *ccnt[2];
+  for (auto &c : ccnt) c = cv.take<uint32_t>(nch);
+  uint32_t *big[2];  // large nodes of a level and of the next
+  for (auto &b : big) b = cv.take<uint32_t>(m / KD_WAVE_MAX + 1);
+  BuildState *st = cv.take<BuildState>(1);
+  uint32_t *order = voxel_order ? cv.take<uint32_t>(m) : perm_dev;  // photons by voxel
+  float *pos_s = voxel_order ? cv.take<float>(3 * m) : nullptr;
+  float *nrm_s = voxel_order && normal_dev ? cv.take<float>(3 * m) : nullptr;
 
-  NPG_HIP_CHECK(ctx, hipMemsetAsync(ctr, 0, 16, s));
+  NPG_HIP_CHECK(ctx, hipMemsetAsync(st, 0, sizeof(BuildState), s));
   hipLaunchKernelGGL(fill_i32_kernel, dim3(grid_for(nvox)), dim3(256), 0, s, cell_root_dev, nvox, -1);
   NPG_HIP_CHECK(ctx, hipGetLastError());
-  uint32_t n0 = 0;
+  const int last = params->max_depth + 1;
   if (n) {
+    NPG_HIP_CHECK(ctx, hipMemsetAsync(ccnt[0], 0, 4 * nch, s));
+    NPG_HIP_CHECK(ctx, hipMemsetAsync(ccnt[1], 0, 4 * nch, s));
     hipLaunchKernelGGL(kd_keys_kernel, dim3(grid_for(n)), dim3(256), 0, s, g, pos_dev, normal_dev, n, valid_dev,
                        sent, key, ctx->err_dev);
     NPG_HIP_CHECK(ctx, hipGetLastError());
-    int bits = 1;
-    while (bits < 32 && (1ull << bits) <= (uint64_t)sent) ++bits;
-    NPG_HIP_CHECK(ctx, npg_radix_sort(key, nullptr, n, bits, ks, perm_dev, work, s));
-    hipLaunchKernelGGL(kd_seg_kernel, dim3(grid_for(n)), dim3(256), 0, s, ks, n, sent, flag, ctr);
+    int vbits = 1;
+    while (vbits < 32 && (1ull << vbits) <= (uint64_t)sent) ++vbits;
+    NPG_HIP_CHECK(ctx, npg_radix_sort(key, nullptr, n, vbits, ks, order, work, s));
+    hipLaunchKernelGGL(kd_seg_kernel, dim3(grid_for((n + SEG_G - 1) / SEG_G)), dim3(256), 0, s, ks, n, sent, bits, cnt,
+                       voxel_order ? key : nullptr, st);
     NPG_HIP_CHECK(ctx, hipGetLastError());
-    NPG_HIP_CHECK(ctx, npg_scan_u32(flag, n, seg, stmp, s));
-    NPG_HIP_CHECK(ctx, hipMemcpyAsync(&n0, seg + n, 4, hipMemcpyDeviceToHost, s));
-    uint32_t errw = 0;
-    rc = take_err(ctx, s, &errw);  // synchronises: n0 is now valid
-    if (rc) return rc;
-    if (errw & ERR_RANGE) return npg_fail(ctx, NPG_E_RANGE, "build_kdgrid: a position or normal is not finite");
-    if (n0 > max_leaves)
-      return npg_fail(ctx, NPG_E_CAPACITY, "build_kdgrid: %u voxel roots exceed max_leaves %u", n0, max_leaves);
-    if (n0) {
-      hipLaunchKernelGGL(kd_roots_kernel, dim3(grid_for(n)), dim3(256), 0, s, g, ks, flag, seg, n, lv[0],
-                         cell_root_dev);
-      hipLaunchKernelGGL(kd_root_counts_kernel, dim3((n0 + 255) / 256), dim3(256), 0, s, lv[0], n0, ctr);
+    NPG_HIP_CHECK(ctx, npg_scan_u32(cnt, nw, rank, stmp, s));
+    hipLaunchKernelGGL(kd_roots_kernel, dim3(grid_for(nw)), dim3(256), 0, s, g, ks, bits, rank, nw, max_leaves, lv[0],
+                       cell_root_dev, st);
+    NPG_HIP_CHECK(ctx, hipMemsetAsync(bits, 0, 4 * nw, s));  // from here on: the leaf starts
+    // most nodes a level can have: one photon each, and twice the level above
+    uint64_t bound = std::min(std::min<uint64_t>(n, cap), nvox);
+    hipLaunchKernelGGL(kd_root_counts_kernel, dim3((unsigned)std::min<uint64_t>((bound + 255) / 256, 1024)), dim3(256),
+                       0, s, lv[0], st, big[0]);
+    NPG_HIP_CHECK(ctx, hipGetLastError());
+    // what the levels permute: the photons, or their places in voxel order (the
+    // unsorted keys' memory)
+    uint32_t *lperm = voxel_order ? key : perm_dev;
+    const uint32_t big_blocks = (uint32_t)std::min<uint64_t>(n / KD_WAVE_MAX, 512);  // 2 per CU
+    for (int depth = 0; depth <= params->max_depth; ++depth) {
+      Level &cur = lv[depth & 1], &nxt = lv[(depth + 1) & 1];
+      uint32_t *bg = big[depth & 1], *bg_next = big[(depth + 1) & 1];
+      const bool copies = voxel_order && depth > 0;  // the first level has left them
+      const SelArgs sa{copies ? pos_s : pos_dev, copies ? nrm_s : normal_dev, copies ? lperm : order, cur,
+                       depth < params->max_depth, params->split_count, params->split_var, tkey, sflag, sel,
+                       ccnt[depth & 1], ctx->err_dev, depth ? nullptr : pos_s, depth ? nullptr : nrm_s};
+      if (big_blocks)
+        hipLaunchKernelGGL(kd_select_big_kernel, dim3(big_blocks), dim3(KD_BIG), 0, s, sa, &st->lv[depth], bg);
+      hipLaunchKernelGGL(kd_select_kernel, dim3((unsigned)std::min<uint64_t>((bound + 3) / 4, KD_GRID)),
+                         dim3(KD_THREADS), 0, s, sa, &st->lv[depth]);
+      hipLaunchKernelGGL(kd_lists_kernel, dim3((unsigned)std::min<uint64_t>((bound + KD_CHUNK - 1) / KD_CHUNK, 256)),
+                         dim3(256), 0, s, cur, st, depth, max_leaves, sflag, ccnt[depth & 1], ccnt[(depth + 1) & 1],
+                         slist, lstart, lnode, bits);
+      if (depth < params->max_depth) {
+        if (big_blocks)
+          hipLaunchKernelGGL(kd_partition_big_kernel, dim3(big_blocks), dim3(KD_BIG), 0, s, lperm, pa, tkey, cur,
+                             nxt, bg, sflag, sel, st, depth, bg_next, nodes_dev);
+        hipLaunchKernelGGL(kd_partition_kernel, dim3((unsigned)std::min<uint64_t>((bound + 3) / 4, KD_GRID)),
+                           dim3(KD_THREADS), 0, s, lperm, tkey, cur, nxt, slist, sel, st, depth, bg_next, nodes_dev);
+      }
       NPG_HIP_CHECK(ctx, hipGetLastError());
+      bound = std::min<uint64_t>(2 * bound, std::min<uint64_t>(n, cap));
     }
-  }
-  // levels
-  uint32_t active = n0, nodes_total = n0;
-  uint64_t emitted = 0;
-  for (int depth = 0; active > 0; ++depth) {
-    Level &cur = lv[depth & 1], &nxt = lv[(depth + 1) & 1];
-    NPG_HIP_CHECK(ctx, hipMemsetAsync(ctr + 1, 0, 4, s));
-    hipLaunchKernelGGL(kd_select_wave_kernel, dim3((active + 3) / 4), dim3(KD_THREADS), 0, s, pos_dev, normal_dev,
-                       perm_dev, cur, active, depth, params->max_depth, params->split_count, params->split_var, tkey,
-                       sflag, sel, big, ctr + 1, ctx->err_dev);
-    hipLaunchKernelGGL(kd_select_kernel, dim3(std::min<uint32_t>(active, 2048)), dim3(KD_THREADS), 0, s, pos_dev,
-                       normal_dev, perm_dev, cur, big, ctr + 1, depth, params->max_depth, params->split_count,
-                       params->split_var, tkey, sflag, sel, ctx->err_dev);
+    if (voxel_order)
+      hipLaunchKernelGGL(kd_final_kernel, dim3(grid_for(n)), dim3(256), 0, s, order, lperm, n, st, perm_dev);
+    hipLaunchKernelGGL(kd_popc_kernel, dim3(grid_for(nw)), dim3(256), 0, s, bits, nw, cnt);
     NPG_HIP_CHECK(ctx, hipGetLastError());
-    NPG_HIP_CHECK(ctx, npg_scan_u32(sflag, active, srank, stmp, s));
-    uint32_t nsplit = 0;
-    NPG_HIP_CHECK(ctx, hipMemcpyAsync(&nsplit, srank + active, 4, hipMemcpyDeviceToHost, s));
-    NPG_HIP_CHECK(ctx, hipStreamSynchronize(s));
-    // leaves so far + this level's + at least one per child: the bound keeps
-    // the next level's records and every leaf slot within max_leaves
-    const uint32_t leaf_base = (uint32_t)emitted;
-    emitted += active - nsplit;
-    if (emitted + 2ull * nsplit > cap)
-      return npg_fail(ctx, NPG_E_CAPACITY, "build_kdgrid: more than max_leaves %u leaves", max_leaves);
-    hipLaunchKernelGGL(kd_lists_kernel, dim3((active + 255) / 256), dim3(256), 0, s, cur, active, sflag, srank, big,
-                       lstart, lnode, leaf_base);
-    if (nsplit)
-      hipLaunchKernelGGL(kd_partition_kernel, dim3(nsplit), dim3(KD_THREADS), 0, s, perm_dev, pa, tkey, cur, nxt, big,
-                         srank, sel, nodes_total, nodes_dev);
-    NPG_HIP_CHECK(ctx, hipGetLastError());
-    nodes_total += 2 * nsplit;
-    active = 2 * nsplit;
+    NPG_HIP_CHECK(ctx, npg_scan_u32(cnt, nw, rank, stmp, s));
   }
-  uint32_t hc[2] = {0, 0}, errw = 0;
-  NPG_HIP_CHECK(ctx, hipMemcpyAsync(hc, ctr, 8, hipMemcpyDeviceToHost, s));
-  rc = take_err(ctx, s, &errw);
-  if (rc) return rc;
-  // the key pass has checked every position and every normal it needed
-  if (errw & ERR_RANGE) return npg_fail(ctx, NPG_E_RANGE, "build_kdgrid: a normal is not finite");
-  const uint32_t L = (uint32_t)emitted;
-  if (L > max_leaves)
-    return npg_fail(ctx, NPG_E_CAPACITY, "build_kdgrid: %u leaves exceed max_leaves %u", L, max_leaves);
-  if (L) {
-    int bits = 1;
-    while (bits < 32 && (1ull << bits) <= (uint64_t)hc[0]) ++bits;
-    NPG_HIP_CHECK(ctx, npg_radix_sort(lstart, lnode, L, bits, lstart_s, lnode_s, work, s));
-  }
-  hipLaunchKernelGGL(kd_leaves_kernel, dim3(L ? (L + 255) / 256 : 1), dim3(256), 0, s, lstart_s, lnode_s, L, ctr,
-                     leaf_off_dev, nodes_dev);
+  hipLaunchKernelGGL(kd_leaves_kernel, dim3((unsigned)std::min<uint64_t>((std::min<uint64_t>(m, cap) + 255) / 256, 1024)),
+                     dim3(256), 0, s, lstart, lnode, bits, rank, last, st, leaf_off_dev, nodes_dev, ctx->err_dev);
   NPG_HIP_CHECK(ctx, hipGetLastError());
+  BuildState h;
+  NPG_HIP_CHECK(ctx, hipMemcpyAsync(&h, st, sizeof h, hipMemcpyDeviceToHost, s));
   NPG_HIP_CHECK(ctx, hipStreamSynchronize(s));
-  *n_leaves_out = L;
-  *n_nodes_out = nodes_total;
+  if (h.err) NPG_HIP_CHECK(ctx, hipMemsetAsync(ctx->err_dev, 0, 4, s));
+  if (h.err & ERR_RANGE) return npg_fail(ctx, NPG_E_RANGE, "build_kdgrid: a position or normal is not finite");
+  if (h.roots > max_leaves)
+    return npg_fail(ctx, NPG_E_CAPACITY, "build_kdgrid: %u voxel roots exceed max_leaves %u", h.roots, max_leaves);
+  if (h.over) return npg_fail(ctx, NPG_E_CAPACITY, "build_kdgrid: more than max_leaves %u leaves", max_leaves);
+  *n_leaves_out = h.lv[last].leaf_base;
+  *n_nodes_out = h.lv[last].nodes;
   return NPG_OK;
 }
 
