@@ -1130,16 +1130,25 @@ extern "C" int npg_build_kdgrid(npg_ctx *ctx, const npg_kdgrid_params *params, c
   const uint64_t nw = (m + 31) / 32;         // words of a bitmap over the photons
   const uint64_t nch = (cap / KD_CHUNK + 1) * KD_CSTEP;  // split counters of a level
   const size_t sort_work = npg_radix_work_bytes(m);
-  const bool voxel_order = params->max_depth >= 2 && n <= VOXEL_ORDER_MAX;
   size_t bytes = 4 * npg_align(4 * m) + sort_work;
   bytes += 3 * npg_align(4 * (nw + 1)) + npg_align(4 * npg_scan_tmp_words(nw));
   bytes += 2 * (3 * npg_align(4 * cap) + npg_align(48 * cap));        // two levels
   bytes += 2 * npg_align(4 * cap) + npg_align(12 * cap);              // sflag, split list, sel
   bytes += 2 * npg_align(4 * cap) + 2 * npg_align(4 * nch);           // leaves, split counters
   bytes += 2 * npg_align(4 * (m / KD_WAVE_MAX + 1)) + npg_align(sizeof(BuildState));
-  if (voxel_order) bytes += npg_align(4 * m) + (normal_dev ? 2 : 1) * npg_align(12 * m);
+  // The copies are left out where the memory for them is not there, and under a
+  // budget unless the scratch is that large already: what fitted it before a
+  // build, or fits it after, does not depend on them.
+  const size_t copies_bytes = npg_align(4 * m) + (normal_dev ? 2 : 1) * npg_align(12 * m);
+  bool voxel_order = params->max_depth >= 2 && n <= VOXEL_ORDER_MAX &&
+                     (!ctx->budget || bytes + copies_bytes <= ctx->scratch_bytes);
   void *scr = nullptr;
-  rc = npg_scratch(ctx, bytes, s, &scr);
+  rc = npg_scratch(ctx, bytes + (voxel_order ? copies_bytes : 0), s, &scr);
+  if (rc && voxel_order) {
+    (void)hipGetLastError();  // the failed allocation
+    voxel_order = false;
+    rc = npg_scratch(ctx, bytes, s, &scr);
+  }
   if (rc) return rc;
   Carver cv(scr);
   uint32_t *key = cv.take<uint32_t>(m), *ks = cv.take<uint32_t>(m);

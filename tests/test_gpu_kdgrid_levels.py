@@ -60,3 +60,20 @@ def test_many_nodes(ctx, npg, res, n, T, D):
             npg.build_kdgrid(ctx, prm, *args, max_leaves=cap)
         assert e.value.code == npg.E_CAPACITY
     _check(ctx, npg, p, nrm, valid, res, T, 0.3, D, 0)  # the context is as good as before
+
+
+def test_budget(ctx, npg):
+    """A context with a budget builds without the copies in voxel order, and
+    gives the same grid as one without."""
+    rng = np.random.default_rng(9)
+    n, res, L = 300000, 9, 20000
+    p = rng.random((n, 3)).astype(np.float32)
+    nrm = synth.unit_vectors(rng, n).astype(np.float32)
+    prm = npg.kdgrid_params(res, (0.0, 0.0, 0.0), (1.0, 1.0, 1.0), 100.0, 0.3, 8)
+    small = npg.Context(0, 24 << 20)  # four arrays of n words, the sort's and the levels'; the copies are 8.4 MB more
+    a = npg.build_kdgrid(ctx, prm, tf(p), tf(nrm), max_leaves=L)
+    b = npg.build_kdgrid(small, prm, tf(p), tf(nrm), max_leaves=L)
+    assert a["n_leaves"] == b["n_leaves"] and a["n_nodes"] == b["n_nodes"]
+    for k in ("perm", "leaf_off", "cell_root", "nodes"):
+        assert torch.equal(a[k], b[k]), k
+    small.close()
