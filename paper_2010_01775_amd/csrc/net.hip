@@ -366,8 +366,8 @@ __device__ __forceinline__ double src_at(const Src &s, int leaf, int y, int x, i
 // 9/S for the S valid in-map taps (zero output where S = 0), then bias and
 // the activation.
 //
-// One workgroup per tile of TR x TW output pixels of one leaf (TW = min(W,
-// 256), TR = min(H, 256 / TW); grid = (tiles per leaf, leaves)).  The tile
+// One workgroup per tile of TR x TW output pixels of one leaf (up to 256
+// pixels, 16 x 16 where the map has them; grid = (tiles per leaf, leaves)).  The tile
 // and its one-pixel halo are normalised once into LDS as four values of the
 // accumulation type (binary64 in FP32 mode, so the normalised maps are never
 // rounded to float32; float in BF16 mode); bins without photons at t and
@@ -2018,8 +2018,12 @@ struct Runner {
       ctx->conv_flops[1] += 2.0 * Lc * H * W * y.cout * 5.0 * 9.0;
       if (y.k != 3 || y.cin != 5 || (act != ACT_RELU && act != ACT_ELU) || head || res || prec == NPG_FP8)
         return npg_fail(ctx, NPG_E_ARG, "internal: five-channel first layer");
-      // tile of TR x TW pixels per workgroup (H, W powers of two, 4..1024)
-      const int TW = std::min(W, 256), TR = std::min(H, 256 / TW);
+      // tile of TR x TW pixels per workgroup (H, W powers of two, 4..1024),
+      // as square as the map lets it be: 16 x 16 stages 1.27 pixels for each
+      // of its own, 2 x 128 (rows of a 128-wide map) 2.03.  Staging is two u64
+      // to binary64 conversions and four products a pixel: 600 leaves of
+      // 64x128, bf16: 163 -> 149 us.
+      const int TW = std::min(W, std::max(16, 256 / H)), TR = std::min(H, 256 / TW);
       if ((TR + 2) * (TW + 2) > F5_LDS || H % TR || W % TW)
         return npg_fail(ctx, NPG_E_ARG, "internal: five-channel tile %dx%d", TR, TW);
       const dim3 grid((unsigned)((H / TR) * (W / TW)), (unsigned)Lc);

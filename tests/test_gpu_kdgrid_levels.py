@@ -69,7 +69,7 @@ def test_budget(ctx, npg):
     n, res, L = 300000, 9, 20000
     p = rng.random((n, 3)).astype(np.float32)
     nrm = synth.unit_vectors(rng, n).astype(np.float32)
-    prm = npg.kdgrid_params(res, (0.0, 0.0, 0.0), (1.0, 1.0, 1.0), 100.0, 0.3, 8)
+    prm = npg.kdgrid_params(res, (0.0, 0.0, 0.0), (1.0, 1.0, 1.0), 100.0, 0.3, 4)  # at most 16 leaves a voxel
     small = npg.Context(0, 24 << 20)  # four arrays of n words, the sort's and the levels'; the copies are 8.4 MB more
     a = npg.build_kdgrid(ctx, prm, tf(p), tf(nrm), max_leaves=L)
     b = npg.build_kdgrid(small, prm, tf(p), tf(nrm), max_leaves=L)
