@@ -13,7 +13,7 @@
 //                first finest cell and exists if its count is non-zero;
 //   4. number:   exclusive prefix of the leaf-start flags = leaf ids in
 //                Morton order; leaf CSR offsets are the cell start offsets;
-//   5. permute:  stable LSD radix sort of (leaf id, photon index), 8-bit
+//   5. permute:  stable LSD radix sort of (leaf id, photon index), up to 8-bit
 //                digits; ranks inside a wavefront come from ballots over the
 //                digit bits, so equal keys keep their input order.
 #include "npg_internal.h"

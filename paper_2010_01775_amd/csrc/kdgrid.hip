@@ -346,9 +346,9 @@ __device__ __forceinline__ void select_group(const SelArgs &a, uint32_t j, uint3
     if (!split && nrm) {
       long long s[3] = {0, 0, 0};
       bool bad = false;
-      for (uint32_t i = threadIdx.x; i < M; i += KD_BIG) {
+      for (uint64_t i = threadIdx.x; i < M; i += KD_BIG) {
         const f32x3 v = load3(nrm, perm[start + i]);
-        if (a.nrm_s) store3(a.nrm_s, start + i, v);
+        if (a.nrm_s) store3(a.nrm_s, start + (uint32_t)i, v);
         add_qnormal(v, s, &bad);
       }
       tested = true;
@@ -366,7 +366,7 @@ __device__ __forceinline__ void select_group(const SelArgs &a, uint32_t j, uint3
     // keys of the split axis, and their range: bits above the highest one
     // where min and max differ are common to every key (and to the median)
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0;
-    for (uint32_t i0 = threadIdx.x; i0 < M; i0 += 4 * KD_BIG) {  // four keys in flight per lane
+    for (uint64_t i0 = threadIdx.x; i0 < M; i0 += 4 * KD_BIG) {  // four keys in flight per lane
       uint32_t ph[4];
       f32x3 x[4] = {NO3, NO3, NO3, NO3}, v[4] = {NO3, NO3, NO3, NO3};
 #pragma unroll
@@ -380,7 +380,7 @@ __device__ __forceinline__ void select_group(const SelArgs &a, uint32_t j, uint3
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         if (ph[q] == KD_NONE) continue;
-        const uint32_t at = start + i0 + q * KD_BIG, k = okey(axis_of(x[q], axis));
+        const uint32_t at = start + (uint32_t)i0 + q * KD_BIG, k = okey(axis_of(x[q], axis));
         tkey[at] = k;
         if (a.pos_s) store3(a.pos_s, at, x[q]);
         if (copy_n) store3(a.nrm_s, at, v[q]);
@@ -415,7 +415,7 @@ __device__ __forceinline__ void select_group(const SelArgs &a, uint32_t j, uint3
       const uint32_t dmask = (2u << (hi - sh)) - 1u;
       if (threadIdx.x < 256) hist[threadIdx.x] = 0;
       __syncthreads();
-      for (uint32_t i0 = threadIdx.x; i0 < M; i0 += 4 * KD_BIG) {
+      for (uint64_t i0 = threadIdx.x; i0 < M; i0 += 4 * KD_BIG) {
         uint32_t k[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) k[q] = i0 + q * KD_BIG < M ? tkey[start + i0 + q * KD_BIG] : 0u;
@@ -850,20 +850,20 @@ __device__ __forceinline__ void partition_node(uint32_t *__restrict__ perm, uint
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
   uint32_t lbase = 0;  // left photons of the rounds before
-  for (uint32_t r0 = 0; r0 < M; r0 += ROUND) {
-    const int groups = (int)((min(M - r0, ROUND) + NT - 1) / NT);
+  for (uint64_t r0 = 0; r0 < M; r0 += ROUND) {
+    const int groups = (int)((min(M - (uint32_t)r0, ROUND) + NT - 1) / NT);
     uint32_t ph[PART_G], tk[PART_G];
     uint64_t bl[PART_G];
 #pragma unroll
     for (int g = 0; g < PART_G; ++g)
       if (g < groups) {
-        const uint32_t i = r0 + g * NT + threadIdx.x;
+        const uint64_t i = r0 + g * NT + threadIdx.x;
         tk[g] = i < M ? tkey[start + i] : 0xFFFFFFFFu;
         ph[g] = i < M ? perm[start + i] : 0u;
       }
 #pragma unroll
     for (int g = 0; g < PART_G; ++g) {
-      const uint32_t i = r0 + g * NT + threadIdx.x;
+      const uint64_t i = r0 + g * NT + threadIdx.x;
       bl[g] = g < groups ? __ballot(i < M && tk[g] < key) : 0ull;
       if (lane == 0) wl[g * NW + wave] = (uint32_t)__popcll(bl[g]);
     }
@@ -895,10 +895,10 @@ __device__ __forceinline__ void partition_node(uint32_t *__restrict__ perm, uint
 #pragma unroll
     for (int g = 0; g < PART_G; ++g)
       if (g < groups) {
-        const uint32_t i = r0 + g * NT + threadIdx.x;
+        const uint64_t i = r0 + g * NT + threadIdx.x;
         const uint32_t l = lbase + wl[g * NW + wave] + (uint32_t)__popcll(bl[g] & below);
         if (i < M) {
-          const uint32_t dst = tk[g] < key ? l : less + (i - l);
+          const uint32_t dst = tk[g] < key ? l : less + ((uint32_t)i - l);
           tmp[start + dst] = ph[g];
         }
       }
@@ -906,7 +906,7 @@ __device__ __forceinline__ void partition_node(uint32_t *__restrict__ perm, uint
     __syncthreads();
   }
   // every read of the segment is done (barrier above): write it in place
-  for (uint32_t i = threadIdx.x; i < M; i += NT) perm[start + i] = tmp[start + i];
+  for (uint64_t i = threadIdx.x; i < M; i += NT) perm[start + i] = tmp[start + i];
   __syncthreads();  // wl is free for the next node
 }
 
