@@ -26,8 +26,8 @@ __device__ __forceinline__ int quad_xor(int v) {  // the value of lane ^ X, X = 
 constexpr int WIN_MIN = 18;
 
 // Eight table entries t[a .. a+m] (m = 7, or fewer on short rows) around
-// entry g, loaded in one memory round trip.  Rows of 16 to 18 entries load a
-// 16-byte aligned window as two 16-byte pieces (it starts 3 to 6 entries
+// entry g, loaded in one memory round trip.  Rows of at least 16 entries load
+// a 16-byte aligned window as two 16-byte pieces (it starts 3 to 6 entries
 // below g and is moved by 4 entries to stay inside the row); shorter rows
 // load eight clamped single entries.  A load instruction whose 64 lanes hit
 // 64 different lines costs the same at any width, so the wide loads quarter
@@ -67,7 +67,8 @@ __device__ __forceinline__ void load_window(const float *__restrict__ t, int n, 
 // window brackets about a third of the searches and the second most of the
 // rest, where galloping outwards from the first window took several
 // dependent loads: 1e8 samples 10.4 -> 7.6 ms.)  The answer is that of
-// plain bisection.
+// plain bisection.  Each lane by itself: for rows shorter than WIN_MIN, and in
+// calls that wide_search leaves to it.
 __device__ __forceinline__ int last_le(const float *__restrict__ t, int n, float u, float *tl, float *th) {
   int lo = 0, hi = n;           // t[lo] <= u < t[hi]
   float tlo = 0.0f, thi = 1.0f;  // t[lo], t[hi]
@@ -238,6 +239,7 @@ __device__ __forceinline__ int wave_last_le(const float *__restrict__ t, int n, 
 // The guided sample of leaf l from (u1, u2): direction, the table pdf of the
 // sampled bin and the bin, for the lanes with `act` (their leaf and uniforms
 // are valid); every lane of the wavefront calls it.
+template <bool WIDE>
 __device__ __forceinline__ void guided_sample(const float *__restrict__ pdf, const float *__restrict__ marg,
                                               const float *__restrict__ cond, uint32_t l, int H, int W,
                                               float u1, float u2, bool act, uint4 *slot, float *d, float *p,
@@ -248,9 +250,9 @@ __device__ __forceinline__ void guided_sample(const float *__restrict__ pdf, con
   const float dphi = 6.283185307179586f / (float)W;
   const float *M = marg + (size_t)l * (H + 1);
   float m0, m1, c0, c1;
-  const int i = wave_last_le(M, H, u1, act, slot, &m0, &m1);
+  const int i = WIDE ? wave_last_le(M, H, u1, act, slot, &m0, &m1) : act ? last_le(M, H, u1, &m0, &m1) : 0;
   const float *C = cond + ((size_t)l * H + i) * (W + 1);
-  const int j = wave_last_le(C, W, u2, act, slot, &c0, &c1);
+  const int j = WIDE ? wave_last_le(C, W, u2, act, slot, &c0, &c1) : act ? last_le(C, W, u2, &c0, &c1) : 0;
   if (!act) return;
   float t1 = (u1 - m0) / (m1 - m0);
   float t2 = (u2 - c0) / (c1 - c0);
@@ -279,12 +281,13 @@ __device__ __forceinline__ void guided_sample(const float *__restrict__ pdf, con
 // lane each (coalesced 4-byte pieces).  No workgroup barrier: the searches of
 // the four wavefronts take different numbers of rounds, and none waits for
 // the slowest.
+template <bool WIDE>
 __global__ __launch_bounds__(256) void sample_kernel(
     const float *__restrict__ pdf, const float *__restrict__ marg, const float *__restrict__ cond,
     uint32_t L, int H, int W, const uint32_t *__restrict__ leaf, const float2 *__restrict__ u, uint64_t n,
     float *__restrict__ dir, float *__restrict__ pdf_out, uint32_t *__restrict__ bin_out, uint32_t *err) {
   __shared__ float4 sdir[4][48];  // 64 directions of 3 floats for each wavefront
-  __shared__ uint4 slot[4][64];
+  __shared__ uint4 slot[WIDE ? 4 : 1][WIDE ? 64 : 1];
   const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
   float *sd = reinterpret_cast<float *>(sdir[wave]);
   const bool dir16 = (reinterpret_cast<uintptr_t>(dir) & 15) == 0;
@@ -306,7 +309,7 @@ __global__ __launch_bounds__(256) void sample_kernel(
         act = true;
       }
     }
-    guided_sample(pdf, marg, cond, l, H, W, uu.x, uu.y, act, slot[wave], d, &p, &b);
+    guided_sample<WIDE>(pdf, marg, cond, l, H, W, uu.x, uu.y, act, slot[WIDE ? wave : 0], d, &p, &b);
     if (q < n) {
       pdf_out[q] = p;
       if (bin_out) bin_out[q] = b;
@@ -380,13 +383,14 @@ __device__ __forceinline__ float mis_mixture(float a, float nx, float ny, float 
   return fmaf(a, pb, (1.0f - a) * g);
 }
 
+template <bool WIDE>
 __global__ __launch_bounds__(256) void sample_mis_kernel(
     const float2 *__restrict__ bnd, const float *__restrict__ pdf, const float *__restrict__ marg,
     const float *__restrict__ cond, uint32_t L, int H, int W, const float *__restrict__ alpha,
     const uint32_t *__restrict__ leaf, const float *__restrict__ normal, const float *__restrict__ u, uint64_t n,
     float *__restrict__ dir, float *__restrict__ pdf_out, uint8_t *__restrict__ strat, uint32_t *err) {
   __shared__ float2 q4[256];
-  __shared__ uint4 slot[4][64];
+  __shared__ uint4 slot[WIDE ? 4 : 1][WIDE ? 64 : 1];
   load_quarter(bnd, W, q4);
   __syncthreads();
   const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
@@ -408,7 +412,7 @@ __global__ __launch_bounds__(256) void sample_mis_kernel(
     }
     float w[3], g;
     uint32_t b;
-    guided_sample(pdf, marg, cond, l, H, W, u1, u2, ok && !bsdf, slot[wave], w, &g, &b);
+    guided_sample<WIDE>(pdf, marg, cond, l, H, W, u1, u2, ok && !bsdf, slot[WIDE ? wave : 0], w, &g, &b);
     if (q >= n) continue;
     if (!ok) {
       const float qnan = __int_as_float(0x7fc00000);
@@ -484,11 +488,26 @@ size_t grid_for(uint64_t n) {
   return (size_t)(b < 262144 ? b : 262144);
 }
 
+// Whether a wavefront's searches are done together.  The wide search asks L2
+// for less, but a round of it takes longer (queries, sums and results go
+// through LDS), so on rows that take several rounds it pays only where the
+// memory is what the others wait for: enough queries to fill the chip, and
+// tables that do not stay in an XCD's 4 MiB L2.  128x128 maps, lane by lane
+// against together: 220 thousand queries on 178 leaves 23.0 / 23.5 us, 400
+// thousand 38.0 / 35.2; 3 million on 15 leaves (1 MB) 138 / 147, on 178 209 /
+// 174, on 2851 323 / 263.  Rows of up to 64 bins take one or two rounds:
+// together is faster or the same from 80 thousand queries on (32x32: 16.4 /
+// 16.6, 220 thousand 18.6 / 17.5; MIS on 64x64: 17.4 / 17.2, 3 million 147 /
+// 144).
+bool wide_search(const npg_tables &t, uint64_t n) {
+  return (t.H <= 64 && t.W <= 64) || (n >= (1u << 18) && 4ull * t.L * t.H * (t.W + 1) > (4ull << 20));
+}
+
 }  // namespace
 
 hipError_t launch_sample(const npg_tables &t, const uint32_t *leaf, const float *u, uint64_t n,
                          float *dir, float *pdf, uint32_t *bin, uint32_t *err, hipStream_t s) {
-  hipLaunchKernelGGL(sample_kernel, dim3(grid_for(n)), dim3(256), 0, s, t.pdf_dev, t.marg_dev, t.cond_dev,
+  hipLaunchKernelGGL(wide_search(t, n) ? sample_kernel<true> : sample_kernel<false>, dim3(grid_for(n)), dim3(256), 0, s, t.pdf_dev, t.marg_dev, t.cond_dev,
                      t.L, t.H, t.W, leaf, reinterpret_cast<const float2 *>(u), n, dir, pdf, bin, err);
   return hipGetLastError();
 }
@@ -502,7 +521,7 @@ hipError_t launch_mis_alpha(const float *nu_b, const float *nu_g, const uint32_t
 hipError_t launch_sample_mis(const float2 *bnd, const npg_tables &t, const float *alpha, const uint32_t *leaf,
                              const float *normal, const float *u, uint64_t n, float *dir, float *pdf,
                              uint8_t *strat, uint32_t *err, hipStream_t s) {
-  hipLaunchKernelGGL(sample_mis_kernel, dim3(grid_for(n)), dim3(256), 0, s, bnd, t.pdf_dev, t.marg_dev, t.cond_dev,
+  hipLaunchKernelGGL(wide_search(t, n) ? sample_mis_kernel<true> : sample_mis_kernel<false>, dim3(grid_for(n)), dim3(256), 0, s, bnd, t.pdf_dev, t.marg_dev, t.cond_dev,
                      t.L, t.H, t.W, alpha, leaf, normal, u, n, dir, pdf, strat, err);
   return hipGetLastError();
 }

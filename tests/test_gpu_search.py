@@ -29,6 +29,7 @@ def _row(t, u):
 @pytest.mark.parametrize("L,H,W,shift,n", [
     (3, 8, 16, 0, 1000), (3, 16, 32, 1, 1000), (3, 32, 16, 2, 700), (5, 32, 64, 3, 4097), (2, 64, 128, 7, 4095),
     (2, 128, 32, 13, 1), (2, 256, 256, 15, 5000), (1, 512, 1024, 5, 5000),
+    (70, 128, 128, 3, (1 << 18) + 5), (9, 512, 512, 6, 1 << 18),  # long rows, many queries, tables above 4 MiB
 ])
 def test_search(ctx, npg, orc, L, H, W, shift, n):
     rng = np.random.default_rng(L * H + W)
