@@ -189,7 +189,7 @@ int npg_splat_histograms(npg_ctx *ctx, const float *dir_dev, const uint32_t *w_d
   int rc = npg_set_device(ctx);
   if (rc) return rc;
   NPG_HIP_CHECK(ctx, launch_splat(ctx->bnd_dev, dir_dev, w_dev, perm_dev, leaf_off_dev, L, H, W, energy_dev,
-                                  count_dev, accumulate ? 1 : 0, ctx->err_dev,
+                                  count_dev, accumulate ? 1 : 0, false, ctx->err_dev,
                                   static_cast<hipStream_t>(stream)));
   return NPG_OK;
 }

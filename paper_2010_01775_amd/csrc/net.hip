@@ -2640,7 +2640,8 @@ static int fused_enqueue(npg_ctx *ctx, const npg_model *m, const float *dir, con
   const NetBufs B = carve_net(cv, plan, chunk, R.esz);
   for (size_t l0 = 0; l0 < L; l0 += chunk) {
     const uint32_t Lc = (uint32_t)std::min<size_t>(chunk, L - l0);
-    NPG_HIP_CHECK(ctx, launch_splat(ctx->bnd_dev, dir, w, perm, off + l0, Lc, H, W, energy, nullptr, 0, ctx->err_dev, s));
+    NPG_HIP_CHECK(ctx, launch_splat(ctx->bnd_dev, dir, w, perm, off + l0, Lc, H, W, energy, nullptr, 0, true,
+                                    ctx->err_dev, s));
     NPG_HIP_CHECK(ctx, launch_leaf_scale(energy, Lc, (int)HW, tot, s));
     const Src in{SRC_ENERGY, energy, nullptr, tot, 0, 0};
     rc = net_chunk(R, in, (int)Lc, H, W, dens, B);

@@ -219,9 +219,11 @@ struct npg_leaf_desc {
 
 // ---------------------------------------------------------------- launchers
 // Each returns a hipError_t from the launch.
+// (chain: the network follows on the same stream)
 hipError_t launch_splat(const float2 *bnd, const float *dir, const uint32_t *w, const uint32_t *perm,
                         const uint32_t *off, uint32_t L, int H, int W, uint64_t *energy,
-                        uint32_t *count, int accumulate, uint32_t *err, hipStream_t s);
+                        uint32_t *count, int accumulate, bool chain, uint32_t *err,
+                        hipStream_t s);
 // true if the network's pooling levels divide an H x W map
 bool npg_model_fits(const npg_model *m, int H, int W);
 bool npg_model_fp8_ready(const npg_model *m);

@@ -2,7 +2,7 @@
 // normalisation of the energy map.
 //
 // Splat: one workgroup per (leaf, band of rows), or several per band that each
-// take a slice of the leaf's photons when there are few leaves.  The band's bins live in LDS
+// take a slice of a large leaf's photons when there are few leaves.  The band's bins live in LDS
 // as packed 64-bit words: bits 0..46 accumulate energy, bits 47..63 the
 // photon count.  A photon adds (1 << 47) + w with one LDS atomic.  Packing is
 // exact as long as a round covers at most 2^15 photons (energy < 2^47, count
@@ -49,23 +49,29 @@ struct DescLeaves {
   __device__ const uint32_t *ws(int leaf) const { return d[leaf].w; }
 };
 
-// Slices a leaf of photons [beg, end) is cut into, at most smax: SPLAT_SLICE photons
-// and more each (four per thread of a 512-thread workgroup, below which the
-// loads of one step already cover the leaf).
+// How the leaves of a batch are cut into slices: a leaf of P photons into the
+// most slices n <= smax with n SPLAT_SLICE <= P and n^2 unit <= P (smax 1: no
+// leaf is).
+struct SplatCut {
+  uint32_t smax, unit;
+};
+// Four photons per thread of a 512-thread workgroup: on fewer, the loads of
+// one step already cover the slice.
 constexpr uint32_t SPLAT_SLICE = 2048;
-__device__ __forceinline__ uint32_t splat_slices(uint32_t beg, uint32_t end, uint32_t smax) {
-  return end > beg ? max(1u, min(smax, (end - beg) / SPLAT_SLICE)) : 1u;
+__device__ __forceinline__ uint32_t splat_slices(uint32_t beg, uint32_t end, SplatCut cut) {
+  const uint32_t n = end > beg ? end - beg : 0u;
+  return max(1u, min(min(cut.smax, n / SPLAT_SLICE), (uint32_t)sqrtf((float)(n / cut.unit))));
 }
 
 // Zeroes the maps of the leaves whose slices will be added up in memory.
 template <class LS>
-__global__ __launch_bounds__(256) void splat_zero_kernel(LS src, int HW, uint32_t smax,
+__global__ __launch_bounds__(256) void splat_zero_kernel(LS src, int HW, SplatCut cut,
                                                          uint64_t *__restrict__ energy,
                                                          uint32_t *__restrict__ count) {
   const int leaf = blockIdx.x;
   uint32_t beg, end;
   src.range(leaf, &beg, &end);
-  if (splat_slices(beg, end, smax) == 1) return;
+  if (splat_slices(beg, end, cut) == 1) return;
   const size_t base = (size_t)leaf * HW;
   for (int k = blockIdx.y * 256 + threadIdx.x; k < HW; k += gridDim.y * 256) {
     energy[base + k] = 0;
@@ -73,29 +79,27 @@ __global__ __launch_bounds__(256) void splat_zero_kernel(LS src, int HW, uint32_
   }
 }
 
-// gridDim.z > 1: a leaf of many photons is shared by up to gridDim.z
-// workgroups per band, whose exact sums meet in global integer atomics (the
-// maps hold zeros or the sums to accumulate onto).  One workgroup per leaf
-// is bound by the latency of its photon loads, 0.7 ns per photon, and leaves
-// most of the chip idle on a few leaves: npg_reconstruct_fused of 11 leaves
-// with 30,000 photons on average (BF16, 64x64), 194 us of it the splat, went
-// from 364 to 165 us with slices.
-template <int BPT, int NT, class LS>
+// CUT: a leaf of many photons is shared by several workgroups per band
+// (blockIdx.z), whose exact sums meet in global integer atomics (the maps hold
+// zeros or the sums to accumulate onto).
+template <int BPT, int NT, bool CUT, class LS>
 __global__ __launch_bounds__(NT) void splat_kernel(
-    const float2 *__restrict__ bnd, LS src, int H, int W, int band_rows, uint64_t *__restrict__ energy,
+    const float2 *__restrict__ bnd, LS src, int H, int W, int band_rows, SplatCut cut, uint64_t *__restrict__ energy,
     uint32_t *__restrict__ count, int accumulate, uint32_t *err) {
   extern __shared__ unsigned long long acc[];
   __shared__ float2 q4[256];
   const int leaf = blockIdx.x;
-  uint32_t beg, end;
-  src.range(leaf, &beg, &end);
-  const uint32_t ns = gridDim.z > 1 ? splat_slices(beg, end, gridDim.z) : 1;
-  if (blockIdx.z >= ns) return;
-  if (ns > 1) {
-    const uint32_t n = end - beg, per = n / ns;  // ns > 1: per >= SPLAT_SLICE
-    const uint32_t b0 = beg + blockIdx.z * per;
-    end = blockIdx.z + 1 == ns ? end : b0 + per;
-    beg = b0;
+  uint32_t beg, end, ns = 1;
+  if constexpr (CUT) {
+    src.range(leaf, &beg, &end);
+    ns = splat_slices(beg, end, cut);
+    if (blockIdx.z >= ns) return;
+    if (ns > 1) {
+      const uint32_t per = (end - beg) / ns;
+      const uint32_t b0 = beg + blockIdx.z * per;
+      end = blockIdx.z + 1 == ns ? end : b0 + per;
+      beg = b0;
+    }
   }
   const int row0 = blockIdx.y * band_rows;
   const int nb = band_rows * W;
@@ -109,6 +113,7 @@ __global__ __launch_bounds__(NT) void splat_kernel(
     e[j] = 0ull;
     c[j] = 0u;
   }
+  if constexpr (!CUT) src.range(leaf, &beg, &end);
   const float *dir = src.dirs(leaf);
   const uint32_t *w = src.ws(leaf);
   bool bad = false;
@@ -162,7 +167,7 @@ __global__ __launch_bounds__(NT) void splat_kernel(
   for (int j = 0; j < BPT; ++j) {
     const int k = tid + j * NT;
     if (k < nb) {
-      if (ns > 1) {
+      if (CUT && ns > 1) {
         if (c[j]) {
           atomicAdd(reinterpret_cast<unsigned long long *>(energy + base + k), e[j]);
           if (count) atomicAdd(count + base + k, c[j]);
@@ -178,57 +183,80 @@ __global__ __launch_bounds__(NT) void splat_kernel(
   }
 }
 
-template <int BPT, int NT, class LS>
-hipError_t launch_splat_t(const float2 *bnd, const LS &src, uint32_t L, int H, int W, int band_rows,
+// Whether and how a batch's leaves are cut.  One workgroup takes 1.1 ns per
+// photon of its leaf, and on few leaves the rest of the chip is idle.  The slices
+// of a leaf add their sums in memory: n slices of all L leaves touch n L HW / 16
+// lines of 128 bytes, 12 G lines/s, half as many again with counts.  The two
+// together are least at n^2 = P / unit, unit = L HW / 200; half that here, as the
+// leaves of a batch differ in size and only the large ones are cut.
+// Whole and cut, us: 64x64 maps, 11 leaves of 30,000 photons 42 / 12.5, 128 leaves
+// 48 / 29; 128x128 maps, 11 leaves 32 / 18; lognormal sizes about 3000 on 200 64x64
+// maps 77 / 25.  A leaf of 8000 among 512 stays whole (128x128 maps: 32; 104 when
+// every leaf of 4096 photons was cut, whatever L HW).
+// The zeroing pass costs 2.5 us whatever the photons, which the host does not
+// know.  A splat on its own leaves it out where only leaves of more than the
+// octree's 8192 photons would be cut (64x64 maps: from 193 leaves on; 200 of 300
+// photons 8.9 us queued, 11.5 with the pass).  In front of a network (`chain`)
+// it is 1.5 % of the call at such sizes, and stays for the few large leaves up to
+// 512 leaf bands, from where on the bands fill the chip by themselves.
+SplatCut splat_cut(uint32_t L, int H, int W, int band_rows, bool count, bool chain) {
+  const uint64_t bands = (uint64_t)(H / band_rows);
+  const uint64_t unit = std::max<uint64_t>(1, (uint64_t)L * H * W / (count ? 256 : 384));
+  if (L * bands > 512 || (!chain && 4 * unit > 8192)) return {1, 1};
+  return {(uint32_t)std::min<uint64_t>(64, 1024 / (L * bands)), (uint32_t)unit};
+}
+
+template <int BPT, int NT, bool CUT, class LS>
+hipError_t launch_splat_k(const float2 *bnd, const LS &src, uint32_t L, int H, int W, int band_rows, SplatCut cut,
                           uint64_t *energy, uint32_t *count, int accumulate, uint32_t *err, hipStream_t s) {
-  // Slices while the batch leaves room for them: about 1024 workgroups in
-  // all, at most 64 per leaf (the sums of a leaf's slices meet on the same
-  // addresses).  From 512 leaf bands on the bands fill the chip by
-  // themselves, and the zeroing pass that slices need would only cost.
-  const unsigned bands = (unsigned)(H / band_rows);
-  unsigned slices = 1;
-  if (L <= 512 / bands) {
-    slices = std::min(64u, 1024u / (L * bands));
-    if (!accumulate) {
-      hipLaunchKernelGGL(splat_zero_kernel<LS>, dim3(L, (unsigned)(H * W + 4095) / 4096), dim3(256), 0, s, src, H * W,
-                         slices, energy, count);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
-  }
   const size_t lds = sizeof(unsigned long long) * (size_t)band_rows * W;
   static std::atomic<uint64_t> attr{0};
   if (npg_first_on_device(attr)) {
-    hipError_t e = hipFuncSetAttribute((const void *)splat_kernel<BPT, NT, LS>,
+    hipError_t e = hipFuncSetAttribute((const void *)splat_kernel<BPT, NT, CUT, LS>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize,
                                        SPLAT_MAX_BINS * sizeof(unsigned long long));
     if (e != hipSuccess) return e;
   }
-  dim3 grid(L, bands, slices);
-  hipLaunchKernelGGL((splat_kernel<BPT, NT, LS>), grid, dim3(NT), lds, s, bnd, src, H, W, band_rows,
-                     energy, count, accumulate, err);
+  hipLaunchKernelGGL((splat_kernel<BPT, NT, CUT, LS>), dim3(L, (unsigned)(H / band_rows), cut.smax), dim3(NT), lds, s,
+                     bnd, src, H, W, band_rows, cut, energy, count, accumulate, err);
   return hipGetLastError();
+}
+
+template <int BPT, int NT, class LS>
+hipError_t launch_splat_t(const float2 *bnd, const LS &src, uint32_t L, int H, int W, int band_rows,
+                          uint64_t *energy, uint32_t *count, int accumulate, bool chain, uint32_t *err,
+                          hipStream_t s) {
+  const SplatCut cut = splat_cut(L, H, W, band_rows, count != nullptr, chain);
+  if (cut.smax == 1)
+    return launch_splat_k<BPT, NT, false>(bnd, src, L, H, W, band_rows, cut, energy, count, accumulate, err, s);
+  if (!accumulate) {
+    hipLaunchKernelGGL(splat_zero_kernel<LS>, dim3(L, (unsigned)(H * W + 4095) / 4096), dim3(256), 0, s, src, H * W,
+                       cut, energy, count);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return launch_splat_k<BPT, NT, true>(bnd, src, L, H, W, band_rows, cut, energy, count, accumulate, err, s);
 }
 
 // Maps of up to 4096 bins take 512-thread workgroups (four fit a CU, so a
 // 1024-leaf batch is resident at once); larger bands 1024 threads.
 template <class LS>
 hipError_t launch_splat_any(const float2 *bnd, const LS &src, uint32_t L, int H, int W, uint64_t *energy,
-                            uint32_t *count, int accumulate, uint32_t *err, hipStream_t s) {
+                            uint32_t *count, int accumulate, bool chain, uint32_t *err, hipStream_t s) {
   int band_rows = H;
   while (band_rows * W > SPLAT_MAX_BINS) band_rows >>= 1;
   const int nb = band_rows * W;
   if (nb <= 4096) {
     switch ((nb + 511) / 512) {
-      case 1: return launch_splat_t<1, 512>(bnd, src, L, H, W, band_rows, energy, count, accumulate, err, s);
-      case 2: return launch_splat_t<2, 512>(bnd, src, L, H, W, band_rows, energy, count, accumulate, err, s);
-      case 4: return launch_splat_t<4, 512>(bnd, src, L, H, W, band_rows, energy, count, accumulate, err, s);
-      default: return launch_splat_t<8, 512>(bnd, src, L, H, W, band_rows, energy, count, accumulate, err, s);
+      case 1: return launch_splat_t<1, 512>(bnd, src, L, H, W, band_rows, energy, count, accumulate, chain, err, s);
+      case 2: return launch_splat_t<2, 512>(bnd, src, L, H, W, band_rows, energy, count, accumulate, chain, err, s);
+      case 4: return launch_splat_t<4, 512>(bnd, src, L, H, W, band_rows, energy, count, accumulate, chain, err, s);
+      default: return launch_splat_t<8, 512>(bnd, src, L, H, W, band_rows, energy, count, accumulate, chain, err, s);
     }
   }
   switch ((nb + SPLAT_THREADS - 1) / SPLAT_THREADS) {
-    case 8: return launch_splat_t<8, SPLAT_THREADS>(bnd, src, L, H, W, band_rows, energy, count, accumulate, err, s);
-    default: return launch_splat_t<16, SPLAT_THREADS>(bnd, src, L, H, W, band_rows, energy, count, accumulate, err, s);
+    case 8: return launch_splat_t<8, SPLAT_THREADS>(bnd, src, L, H, W, band_rows, energy, count, accumulate, chain, err, s);
+    default: return launch_splat_t<16, SPLAT_THREADS>(bnd, src, L, H, W, band_rows, energy, count, accumulate, chain, err, s);
   }
 }
 
@@ -261,13 +289,13 @@ __global__ void apply_scale_kernel(const uint64_t *__restrict__ energy, const do
 
 hipError_t launch_splat(const float2 *bnd, const float *dir, const uint32_t *w, const uint32_t *perm,
                         const uint32_t *off, uint32_t L, int H, int W, uint64_t *energy,
-                        uint32_t *count, int accumulate, uint32_t *err, hipStream_t s) {
-  return launch_splat_any(bnd, CsrLeaves{dir, w, perm, off}, L, H, W, energy, count, accumulate, err, s);
+                        uint32_t *count, int accumulate, bool chain, uint32_t *err, hipStream_t s) {
+  return launch_splat_any(bnd, CsrLeaves{dir, w, perm, off}, L, H, W, energy, count, accumulate, chain, err, s);
 }
 
 hipError_t launch_splat_desc(const float2 *bnd, const npg_leaf_desc *d, uint32_t L, int H, int W,
                              uint64_t *energy, uint32_t *err, hipStream_t s) {
-  return launch_splat_any(bnd, DescLeaves{d}, L, H, W, energy, nullptr, 0, err, s);
+  return launch_splat_any(bnd, DescLeaves{d}, L, H, W, energy, nullptr, 0, true, err, s);
 }
 
 hipError_t launch_leaf_scale(const uint64_t *energy, uint32_t L, int HW, double *tot, hipStream_t s) {
