@@ -1762,8 +1762,10 @@ struct Runner {
     size_t wgs;
     if (src.mode == SRC_UPCAT && src.C0 % kc) return false;
     const size_t esz = prec == NPG_FP32 ? sizeof(double) : prec == NPG_FP8 ? 1 : 2;
-    if (lowp_shape(y, src.mode, 1, H, W, &ts, &wgs))  // a tile's leaves behind one buffer resource, as below
-      return (size_t)4 * H * W * std::max(std::max(src.C0, src.C1), y.cout) * esz < ((size_t)1 << 31);
+    // a tile's leaves (one, and up to four on maps narrower than a 16-column
+    // tile) behind one buffer resource, as below
+    if (lowp_shape(y, src.mode, 1, H, W, &ts, &wgs))
+      return (size_t)(W >= 16 ? 1 : 4) * H * W * std::max(std::max(src.C0, src.C1), y.cout) * esz < ((size_t)1 << 31);
     if (!tiling(y, Lc, H, W, t, mw_lim)) return false;
     // the tiles read their input through buffer resources: the bytes of one
     // tile's leaves must stay below 2^31 (offsets at or past 2^31 mean padding)
