@@ -134,9 +134,9 @@ void npg_conv_flops(npg_ctx *ctx, double *matrix, double *vector, int reset);
  *                  the results agree to rounding)
  *   "tile_cap"     largest matrix-core tile, in units of 64 output pixels:
  *                  1, 2, 4 or 8 (a value in between rounds down; default 4,
- *                  but 8 for an 8/16-bit first layer computed in the next
- *                  one's tiles and 2 for FP32-mode layers of up to 32
- *                  channels; few leaves take smaller tiles by themselves;
+ *                  with which an 8/16-bit first layer computed in the next
+ *                  one's tiles takes 8 and FP32-mode layers of up to 32
+ *                  channels 2; few leaves take smaller tiles by themselves;
  *                  a tuned table caps each layer further; testing: every
  *                  tile shape gives identical results)
  * NPG_E_ARG for an unknown name or a negative value. */

@@ -2408,7 +2408,7 @@ Runner make_runner(npg_ctx *ctx, const npg_model *m, npg_precision prec, hipStre
   R.pool_outputs = ctx->opt("pool_outputs", 1) ? 1 : 0;
   const long long cap = ctx->opt("tile_cap", 4);  // testing: pixel tiles of at most 64 * cap
   R.mw_all = cap >= 8 ? 8 : cap >= 4 ? 4 : cap >= 2 ? 2 : 1;
-  if (ctx->opts.count("tile_cap")) {
+  if (R.mw_all != 4) {  // 4, also when set, keeps the layers' own defaults
     R.mw_first = R.mw_all;
     R.mw_narrow = 0;
   }
