@@ -285,7 +285,9 @@ int npg_mark_valid(npg_ctx *ctx, const npg_kdgrid_params *params, const float *p
  * Synchronises `stream`.  A non-finite position, or a non-finite normal of a
  * photon in a valid voxel, returns NPG_E_RANGE; more than max_leaves leaves
  * NPG_E_CAPACITY (outputs
- * unspecified, *n_leaves_out = 0).  n <= 2^32 - 1, max_leaves < 2^29. */
+ * unspecified, *n_leaves_out = 0).  n <= 2^32 - 1, max_leaves < 2^29.
+ * Scratch space: about 37 bytes a photon (33 under a budget, and where the
+ * device has no room for them) and 150 a leaf of max_leaves. */
 int npg_build_kdgrid(npg_ctx *ctx, const npg_kdgrid_params *params, const float *pos_dev,
                      const float *normal_dev, uint64_t n, const uint8_t *valid_dev, uint32_t *perm_dev,
                      uint32_t *leaf_off_dev, int32_t *cell_root_dev, npg_kd_node *nodes_dev, uint32_t max_leaves,

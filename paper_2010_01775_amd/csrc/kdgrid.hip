@@ -229,13 +229,12 @@ __global__ __launch_bounds__(256) void kd_root_counts_kernel(Level lv, BuildStat
   }
 }
 
-// perm from places in voxel order (idx) and the photons in that order
-__global__ __launch_bounds__(256) void kd_final_kernel(const uint32_t *__restrict__ order,
-                                                       const uint32_t *__restrict__ idx, uint64_t n,
+// perm: from places in voxel order to the photons there
+__global__ __launch_bounds__(256) void kd_final_kernel(const uint32_t *__restrict__ order, uint64_t n,
                                                        const BuildState *st, uint32_t *__restrict__ perm) {
   const uint32_t nvalid = st->nvalid;
   for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    perm[i] = order[i < nvalid ? idx[i] : (uint32_t)i];
+    perm[i] = order[i < nvalid ? perm[i] : (uint32_t)i];
 }
 
 // Workgroup-wide sums of three int64 values (exact, so the order is free).
@@ -1077,11 +1076,6 @@ int grid_params(npg_ctx *ctx, const npg_kdgrid_params *p, GridDev *g) {
 // and few enough that a level without nodes costs 5 us.
 constexpr uint64_t KD_GRID = 8192;
 
-// Most photons whose positions and normals are copied into voxel order (24
-// bytes each: 6.4 GB).  Beyond, and for trees of one level, which read each
-// photon once anyway, every level gathers from the caller's arrays.
-constexpr uint64_t VOXEL_ORDER_MAX = 1ull << 28;
-
 }  // namespace
 
 extern "C" int npg_mark_valid(npg_ctx *ctx, const npg_kdgrid_params *params, const float *pts_dev, uint64_t n,
@@ -1130,31 +1124,42 @@ extern "C" int npg_build_kdgrid(npg_ctx *ctx, const npg_kdgrid_params *params, c
   const uint64_t nw = (m + 31) / 32;         // words of a bitmap over the photons
   const uint64_t nch = (cap / KD_CHUNK + 1) * KD_CSTEP;  // split counters of a level
   const size_t sort_work = npg_radix_work_bytes(m);
-  size_t bytes = 4 * npg_align(4 * m) + sort_work;
+  // keys, sorted keys and the sort's memory, and then the copies in their place
+  // (six arrays of words and more against 24 bytes a photon)
+  const size_t sort_bytes = 2 * npg_align(4 * m) + sort_work;
+  size_t bytes = 2 * npg_align(4 * m) + sort_bytes;
   bytes += 3 * npg_align(4 * (nw + 1)) + npg_align(4 * npg_scan_tmp_words(nw));
   bytes += 2 * (3 * npg_align(4 * cap) + npg_align(48 * cap));        // two levels
   bytes += 2 * npg_align(4 * cap) + npg_align(12 * cap);              // sflag, split list, sel
   bytes += 2 * npg_align(4 * cap) + 2 * npg_align(4 * nch);           // leaves, split counters
   bytes += 2 * npg_align(4 * (m / KD_WAVE_MAX + 1)) + npg_align(sizeof(BuildState));
-  // The copies are left out where the memory for them is not there, and under a
+  // Photons are copied into voxel order for trees of more than one level (one
+  // level reads each photon once anyway).  That takes one more array of words
+  // (`order`): 37 bytes a photon, where every level gathering from the caller's
+  // arrays takes 33.  Left out where the device has no room for it, and under a
   // budget unless the scratch is that large already: what fitted it before a
-  // build, or fits it after, does not depend on them.
-  const size_t copies_bytes = npg_align(4 * m) + (normal_dev ? 2 : 1) * npg_align(12 * m);
-  bool voxel_order = params->max_depth >= 2 && n <= VOXEL_ORDER_MAX &&
-                     (!ctx->budget || bytes + copies_bytes <= ctx->scratch_bytes);
+  // build, or fits it after, does not depend on the copies.
+  const size_t with_order = npg_align(bytes + npg_align(4 * m), 1 << 20);
+  bool voxel_order = params->max_depth >= 2 &&
+                     (with_order <= ctx->scratch_bytes || (!ctx->budget && with_order < ctx->kd_no_room));
   void *scr = nullptr;
-  rc = npg_scratch(ctx, bytes + (voxel_order ? copies_bytes : 0), s, &scr);
-  if (rc && voxel_order) {
-    (void)hipGetLastError();  // the failed allocation
+  rc = npg_scratch(ctx, voxel_order ? with_order : bytes, s, &scr);
+  if (rc && voxel_order && hipGetLastError() == hipErrorOutOfMemory) {
+    ctx->kd_no_room = with_order;  // not tried again by later builds
     voxel_order = false;
     rc = npg_scratch(ctx, bytes, s, &scr);
   }
   if (rc) return rc;
   Carver cv(scr);
-  uint32_t *key = cv.take<uint32_t>(m), *ks = cv.take<uint32_t>(m);
   uint32_t *pa = cv.take<uint32_t>(m);  // partition staging
   uint32_t *tkey = cv.take<uint32_t>(m);
-  void *work = cv.take<char>(sort_work);
+  uint32_t *order = voxel_order ? cv.take<uint32_t>(m) : perm_dev;  // photons by voxel
+  Carver sorting(cv.take<char>(sort_bytes)), copies(sorting.base);
+  uint32_t *key = sorting.take<uint32_t>(m), *ks = sorting.take<uint32_t>(m);
+  void *work = sorting.take<char>(sort_work);
+  // written by the first level, when the keys have been read
+  float *pos_s = voxel_order ? copies.take<float>(3 * m) : nullptr;
+  float *nrm_s = voxel_order && normal_dev ? copies.take<float>(3 * m) : nullptr;
   uint32_t *bits = cv.take<uint32_t>(nw + 1), *cnt = cv.take<uint32_t>(nw + 1), *rank = cv.take<uint32_t>(nw + 1);
   uint32_t *stmp = cv.take<uint32_t>(npg_scan_tmp_words(nw));
   Level lv[2];
@@ -1172,9 +1177,6 @@ extern "C" int npg_build_kdgrid(npg_ctx *ctx, const npg_kdgrid_params *params, c
   uint32_t *big[2];  // large nodes of a level and of the next
   for (auto &b : big) b = cv.take<uint32_t>(m / KD_WAVE_MAX + 1);
   BuildState *st = cv.take<BuildState>(1);
-  uint32_t *order = voxel_order ? cv.take<uint32_t>(m) : perm_dev;  // photons by voxel
-  float *pos_s = voxel_order ? cv.take<float>(3 * m) : nullptr;
-  float *nrm_s = voxel_order && normal_dev ? cv.take<float>(3 * m) : nullptr;
 
   NPG_HIP_CHECK(ctx, hipMemsetAsync(st, 0, sizeof(BuildState), s));
   hipLaunchKernelGGL(fill_i32_kernel, dim3(grid_for(nvox)), dim3(256), 0, s, cell_root_dev, nvox, -1);
@@ -1190,7 +1192,7 @@ extern "C" int npg_build_kdgrid(npg_ctx *ctx, const npg_kdgrid_params *params, c
     while (vbits < 32 && (1ull << vbits) <= (uint64_t)sent) ++vbits;
     NPG_HIP_CHECK(ctx, npg_radix_sort(key, nullptr, n, vbits, ks, order, work, s));
     hipLaunchKernelGGL(kd_seg_kernel, dim3(grid_for((n + SEG_G - 1) / SEG_G)), dim3(256), 0, s, ks, n, sent, bits, cnt,
-                       voxel_order ? key : nullptr, st);
+                       voxel_order ? perm_dev : nullptr, st);
     NPG_HIP_CHECK(ctx, hipGetLastError());
     NPG_HIP_CHECK(ctx, npg_scan_u32(cnt, nw, rank, stmp, s));
     hipLaunchKernelGGL(kd_roots_kernel, dim3(grid_for(nw)), dim3(256), 0, s, g, ks, bits, rank, nw, max_leaves, lv[0],
@@ -1201,15 +1203,12 @@ extern "C" int npg_build_kdgrid(npg_ctx *ctx, const npg_kdgrid_params *params, c
     hipLaunchKernelGGL(kd_root_counts_kernel, dim3((unsigned)std::min<uint64_t>((bound + 255) / 256, 1024)), dim3(256),
                        0, s, lv[0], st, big[0]);
     NPG_HIP_CHECK(ctx, hipGetLastError());
-    // what the levels permute: the photons, or their places in voxel order (the
-    // unsorted keys' memory)
-    uint32_t *lperm = voxel_order ? key : perm_dev;
     const uint32_t big_blocks = (uint32_t)std::min<uint64_t>(n / KD_WAVE_MAX, 512);  // 2 per CU
     for (int depth = 0; depth <= params->max_depth; ++depth) {
       Level &cur = lv[depth & 1], &nxt = lv[(depth + 1) & 1];
       uint32_t *bg = big[depth & 1], *bg_next = big[(depth + 1) & 1];
-      const bool copies = voxel_order && depth > 0;  // the first level has left them
-      const SelArgs sa{copies ? pos_s : pos_dev, copies ? nrm_s : normal_dev, copies ? lperm : order, cur,
+      const bool copied = voxel_order && depth > 0;  // the first level has left them
+      const SelArgs sa{copied ? pos_s : pos_dev, copied ? nrm_s : normal_dev, copied ? perm_dev : order, cur,
                        depth < params->max_depth, params->split_count, params->split_var, tkey, sflag, sel,
                        ccnt[depth & 1], ctx->err_dev, depth ? nullptr : pos_s, depth ? nullptr : nrm_s};
       if (big_blocks)
@@ -1221,16 +1220,16 @@ extern "C" int npg_build_kdgrid(npg_ctx *ctx, const npg_kdgrid_params *params, c
                          slist, lstart, lnode, bits);
       if (depth < params->max_depth) {
         if (big_blocks)
-          hipLaunchKernelGGL(kd_partition_big_kernel, dim3(big_blocks), dim3(KD_BIG), 0, s, lperm, pa, tkey, cur,
+          hipLaunchKernelGGL(kd_partition_big_kernel, dim3(big_blocks), dim3(KD_BIG), 0, s, perm_dev, pa, tkey, cur,
                              nxt, bg, sflag, sel, st, depth, bg_next, nodes_dev);
         hipLaunchKernelGGL(kd_partition_kernel, dim3((unsigned)std::min<uint64_t>((bound + 3) / 4, KD_GRID)),
-                           dim3(KD_THREADS), 0, s, lperm, tkey, cur, nxt, slist, sel, st, depth, bg_next, nodes_dev);
+                           dim3(KD_THREADS), 0, s, perm_dev, tkey, cur, nxt, slist, sel, st, depth, bg_next, nodes_dev);
       }
       NPG_HIP_CHECK(ctx, hipGetLastError());
       bound = std::min<uint64_t>(2 * bound, std::min<uint64_t>(n, cap));
     }
     if (voxel_order)
-      hipLaunchKernelGGL(kd_final_kernel, dim3(grid_for(n)), dim3(256), 0, s, order, lperm, n, st, perm_dev);
+      hipLaunchKernelGGL(kd_final_kernel, dim3(grid_for(n)), dim3(256), 0, s, order, n, st, perm_dev);
     hipLaunchKernelGGL(kd_popc_kernel, dim3(grid_for(nw)), dim3(256), 0, s, bits, nw, cnt);
     NPG_HIP_CHECK(ctx, hipGetLastError());
     NPG_HIP_CHECK(ctx, npg_scan_u32(cnt, nw, rank, stmp, s));

@@ -24,6 +24,7 @@ struct npg_ctx {
   void *scratch = nullptr;
   size_t scratch_bytes = 0;
   hipStream_t scratch_stream = nullptr;  // stream that last used the scratch
+  size_t kd_no_room = SIZE_MAX;          // npg_build_kdgrid: a scratch size the device had no room for
   std::string last_error;
   std::map<std::string, long long> opts;          // npg_set_option
   std::map<std::string, std::vector<int>> tune;   // autotuned {chunk, tile cap per conv call}
