@@ -110,6 +110,7 @@ void npg_destroy(npg_ctx *ctx) {
   (void)hipSetDevice(ctx->device);
   for (auto &g : ctx->graphs) (void)hipGraphExecDestroy(g.exec);
   ctx->graphs.clear();
+  if (ctx->kd_active) (void)hipHostFree(ctx->kd_active);
   npg_device_free(ctx, ctx->scratch, ctx->scratch_bytes);
   npg_device_free(ctx, ctx->err_dev, 256 + sizeof(float2) * 256);
   delete ctx;

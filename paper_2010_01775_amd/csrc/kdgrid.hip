@@ -23,10 +23,10 @@
 //   4. leaves ranked by segment start, with a bitmap again: depth-first
 //      order inside a voxel, voxels ascending, since every split keeps its
 //      children inside the parent's segment, first child first.
-// The number of nodes of a level stays on the device (LevelState): the
-// kernels of all levels are queued at once, with grids that stride over
-// however many nodes there are, and the host waits once, at the end.  Waiting
-// for each level's count cost 60 us a level, as much as a level's work from
+// The number of nodes of a level stays on the device (LevelState): the kernels of
+// a level are queued with grids that stride over however many nodes there are,
+// KD_AHEAD levels before the host knows whether the first of them has any.
+// Waiting for each level's count cost 60 us a level, as much as a level's work from
 // the fourth on.  20 million photons in 100^3 voxels, depth 8, with 2 million
 // locations: 3.98 -> 2.84 ms, together with the bitmaps (250 us of flags and
 // scans over the photons -> 60), wavefronts instead of workgroups for small
@@ -120,12 +120,13 @@ struct LevelState {
   uint32_t nbig;       // nodes of more than KD_WAVE_MAX photons
   uint32_t nsplit;     // nodes that split
 };
+constexpr int KD_LEVELS = 18;  // max_depth <= 16, and one more
 struct BuildState {
   uint32_t nvalid;  // photons in valid voxels
   uint32_t roots;
   uint32_t over;  // a level did not fit max_leaves
   uint32_t err;   // the error word when the build ended
-  LevelState lv[18];  // level max_depth + 1 (at most 17) holds the totals
+  LevelState lv[KD_LEVELS];  // the one after the last level queued holds the totals
 };
 
 // bits: 1 at the first photon of each valid voxel's segment; cnt[w] = number
@@ -723,7 +724,8 @@ __global__ __launch_bounds__(KD_THREADS) void kd_select_kernel(SelArgs a, const 
 
 // From the split flags of a level: the list of splitting nodes, the leaf
 // record of every other node (slot leaf_base + number of non-splitting nodes
-// before it) with the bit of its segment start, and the next level's state.
+// before it) with the bit of its segment start, and the next level's state (its
+// number of nodes in the host's memory too, where the host asks for it).
 // Every workgroup takes a range of chunks and sums the counters before it.
 __global__ __launch_bounds__(256) void kd_lists_kernel(Level lv, BuildState *st, int depth, uint32_t cap,
                                                        uint32_t *__restrict__ sflag,
@@ -732,7 +734,7 @@ __global__ __launch_bounds__(256) void kd_lists_kernel(Level lv, BuildState *st,
                                                        uint32_t *__restrict__ split_list,
                                                        uint32_t *__restrict__ leaf_start,
                                                        uint32_t *__restrict__ leaf_node,
-                                                       uint32_t *__restrict__ leaf_bits) {
+                                                       uint32_t *__restrict__ leaf_bits, uint32_t *host_active) {
   __shared__ uint32_t wa[4], wb[4];
   const LevelState cur = st->lv[depth];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -769,6 +771,8 @@ __global__ __launch_bounds__(256) void kd_lists_kernel(Level lv, BuildState *st,
     if (!fits) st->over = 1;
     st->lv[depth].nsplit = fits ? total : 0;
     st->lv[depth + 1].active = fits ? 2 * total : 0;
+    if (host_active)
+      __hip_atomic_store(host_active + depth + 1, fits ? 2 * total : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     st->lv[depth + 1].leaf_base = emitted;
     st->lv[depth + 1].nodes = cur.nodes + 2 * total;
   }
@@ -1073,8 +1077,35 @@ int grid_params(npg_ctx *ctx, const npg_kdgrid_params *p, GridDev *g) {
 
 // Workgroups of a level's kernels, which stride over the nodes there are: more
 // than fit the chip at once (2048), so that nodes of unequal size even out,
-// and few enough that a level without nodes costs 5 us.
+// and few enough that a kernel without nodes costs 5 us, a level 15 to 24.
 constexpr uint64_t KD_GRID = 8192;
+
+// Levels queued before the host looks whether the first of them has nodes: the
+// chip does not wait for the host, and a tree that ends early pays for two levels
+// without nodes.  One level of 100 thousand photons, max_depth 16: 182 us; 377 with
+// all levels queued at once, 305 with a wait for every level's count.  Two ahead
+// leaves gaps on small builds (2000 photons, 5 levels: 10 us more), four cost 10
+// to 20 us more behind the tree's end.
+constexpr int KD_AHEAD = 3;
+
+// The nodes of a level, once kd_lists_kernel of the level above has told.  A
+// value from the device's memory costs a wait and a copy, an event per level
+// 1.5 us on the stream; a word in the host's memory neither.  The wait ends with
+// the stream's work, or its error, at the latest (asked for every few
+// milliseconds: asking holds up the stream).
+int level_nodes(npg_ctx *ctx, int depth, hipStream_t s, uint32_t *nodes) {
+  for (uint32_t spins = 1;; ++spins) {
+    *nodes = __atomic_load_n(ctx->kd_active + depth, __ATOMIC_ACQUIRE);
+    if (*nodes != KD_NONE) return NPG_OK;
+    __builtin_ia32_pause();
+    if (spins % (1u << 18)) continue;
+    const hipError_t e = hipStreamQuery(s);
+    if (e == hipErrorNotReady) continue;
+    NPG_HIP_CHECK(ctx, e);
+    *nodes = __atomic_load_n(ctx->kd_active + depth, __ATOMIC_ACQUIRE);
+    return *nodes != KD_NONE ? NPG_OK : npg_fail(ctx, NPG_E_HIP, "build_kdgrid: level %d was not counted", depth);
+  }
+}
 
 }  // namespace
 
@@ -1178,10 +1209,14 @@ extern "C" int npg_build_kdgrid(npg_ctx *ctx, const npg_kdgrid_params *params, c
   for (auto &b : big) b = cv.take<uint32_t>(m / KD_WAVE_MAX + 1);
   BuildState *st = cv.take<BuildState>(1);
 
+  if (!ctx->kd_active)
+    NPG_HIP_CHECK(ctx, hipHostMalloc(reinterpret_cast<void **>(&ctx->kd_active), sizeof(uint32_t) * KD_LEVELS,
+                                     hipHostMallocCoherent));
+  std::fill_n(ctx->kd_active, KD_LEVELS, KD_NONE);
   NPG_HIP_CHECK(ctx, hipMemsetAsync(st, 0, sizeof(BuildState), s));
   hipLaunchKernelGGL(fill_i32_kernel, dim3(grid_for(nvox)), dim3(256), 0, s, cell_root_dev, nvox, -1);
   NPG_HIP_CHECK(ctx, hipGetLastError());
-  const int last = params->max_depth + 1;
+  int last = 0;  // levels queued: lv[last] has the totals
   if (n) {
     NPG_HIP_CHECK(ctx, hipMemsetAsync(ccnt[0], 0, 4 * nch, s));
     NPG_HIP_CHECK(ctx, hipMemsetAsync(ccnt[1], 0, 4 * nch, s));
@@ -1204,7 +1239,14 @@ extern "C" int npg_build_kdgrid(npg_ctx *ctx, const npg_kdgrid_params *params, c
                        0, s, lv[0], st, big[0]);
     NPG_HIP_CHECK(ctx, hipGetLastError());
     const uint32_t big_blocks = (uint32_t)std::min<uint64_t>(n / KD_WAVE_MAX, 512);  // 2 per CU
-    for (int depth = 0; depth <= params->max_depth; ++depth) {
+    for (last = 0; last <= params->max_depth; ++last) {
+      const int depth = last;
+      if (depth >= KD_AHEAD) {
+        uint32_t nodes = 0;
+        rc = level_nodes(ctx, depth - KD_AHEAD + 1, s, &nodes);
+        if (rc) return rc;
+        if (!nodes) break;  // nor has any level after it
+      }
       Level &cur = lv[depth & 1], &nxt = lv[(depth + 1) & 1];
       uint32_t *bg = big[depth & 1], *bg_next = big[(depth + 1) & 1];
       const bool copied = voxel_order && depth > 0;  // the first level has left them
@@ -1217,7 +1259,7 @@ extern "C" int npg_build_kdgrid(npg_ctx *ctx, const npg_kdgrid_params *params, c
                          dim3(KD_THREADS), 0, s, sa, &st->lv[depth]);
       hipLaunchKernelGGL(kd_lists_kernel, dim3((unsigned)std::min<uint64_t>((bound + KD_CHUNK - 1) / KD_CHUNK, 256)),
                          dim3(256), 0, s, cur, st, depth, max_leaves, sflag, ccnt[depth & 1], ccnt[(depth + 1) & 1],
-                         slist, lstart, lnode, bits);
+                         slist, lstart, lnode, bits, depth + KD_AHEAD <= params->max_depth ? ctx->kd_active : nullptr);
       if (depth < params->max_depth) {
         if (big_blocks)
           hipLaunchKernelGGL(kd_partition_big_kernel, dim3(big_blocks), dim3(KD_BIG), 0, s, perm_dev, pa, tkey, cur,

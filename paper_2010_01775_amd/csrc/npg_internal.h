@@ -24,7 +24,10 @@ struct npg_ctx {
   void *scratch = nullptr;
   size_t scratch_bytes = 0;
   hipStream_t scratch_stream = nullptr;  // stream that last used the scratch
-  size_t kd_no_room = SIZE_MAX;          // npg_build_kdgrid: a scratch size the device had no room for
+  // npg_build_kdgrid: a scratch size the device had no room for; the nodes of
+  // each level, written by the device into pinned host memory
+  size_t kd_no_room = SIZE_MAX;
+  uint32_t *kd_active = nullptr;
   std::string last_error;
   std::map<std::string, long long> opts;          // npg_set_option
   std::map<std::string, std::vector<int>> tune;   // autotuned {chunk, tile cap per conv call}
