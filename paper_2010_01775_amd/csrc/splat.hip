@@ -49,18 +49,15 @@ struct DescLeaves {
   __device__ const uint32_t *ws(int leaf) const { return d[leaf].w; }
 };
 
-// How the leaves of a batch are cut into slices: a leaf of P photons into the
-// most slices n <= smax with n SPLAT_SLICE <= P and n^2 unit <= P (smax 1: no
-// leaf is).
+// How the leaves of a batch are cut into slices (smax 1: no leaf is): a leaf of P
+// photons into min(smax, P / slice, sqrt(P / unit)), given the reciprocals.
 struct SplatCut {
-  uint32_t smax, unit;
+  uint32_t smax;
+  float per_slice, per_unit;
 };
-// Four photons per thread of a 512-thread workgroup: on fewer, the loads of
-// one step already cover the slice.
-constexpr uint32_t SPLAT_SLICE = 2048;
 __device__ __forceinline__ uint32_t splat_slices(uint32_t beg, uint32_t end, SplatCut cut) {
-  const uint32_t n = end > beg ? end - beg : 0u;
-  return max(1u, min(min(cut.smax, n / SPLAT_SLICE), (uint32_t)sqrtf((float)(n / cut.unit))));
+  const float p = end > beg ? (float)(end - beg) : 0.0f;
+  return max(1u, min(cut.smax, (uint32_t)fminf(p * cut.per_slice, sqrtf(p * cut.per_unit))));
 }
 
 // Zeroes the maps of the leaves whose slices will be added up in memory.
@@ -187,12 +184,16 @@ __global__ __launch_bounds__(NT) void splat_kernel(
 // photon of its leaf, and on few leaves the rest of the chip is idle.  The slices
 // of a leaf add their sums in memory: n slices of all L leaves touch n L HW / 16
 // lines of 128 bytes, 12 G lines/s, half as many again with counts.  The two
-// together are least at n^2 = P / unit, unit = L HW / 200; half that here, as the
-// leaves of a batch differ in size and only the large ones are cut.
-// Whole and cut, us: 64x64 maps, 11 leaves of 30,000 photons 42 / 12.5, 128 leaves
-// 48 / 29; 128x128 maps, 11 leaves 32 / 18; lognormal sizes about 3000 on 200 64x64
-// maps 77 / 25.  A leaf of 8000 among 512 stays whole (128x128 maps: 32; 104 when
-// every leaf of 4096 photons was cut, whatever L HW).
+// together are least at n^2 = P / unit with unit = L HW / 200; a sixth of that
+// here, as the leaves of a batch differ in size and only the large ones are cut:
+// requests of 11 to 100 leaves of lognormal sizes about 10 to 30 thousand take
+// within 1 % of what they take with 2048 photons a slice, whatever L HW.  A leaf is
+// not cut below two slices of L HW / 192, so that leaves of one size are not cut
+// for nothing.
+// Whole and cut, us: 64x64 maps, 11 leaves of 30,000 photons 42 / 12.5, 64 leaves
+// 45 / 25; 128x128 maps, 11 leaves 32 / 19; lognormal sizes about 3000 on 200
+// 64x64 maps 77 / 25.  Leaves of 8000 on 128 128x128 maps stay whole (15.5; 39 in
+// slices of 2048: the fused call 357 -> 333).
 // The zeroing pass costs 2.5 us whatever the photons, which the host does not
 // know.  A splat on its own leaves it out where only leaves of more than the
 // octree's 8192 photons would be cut (64x64 maps: from 193 leaves on; 200 of 300
@@ -201,9 +202,11 @@ __global__ __launch_bounds__(NT) void splat_kernel(
 // 512 leaf bands, from where on the bands fill the chip by themselves.
 SplatCut splat_cut(uint32_t L, int H, int W, int band_rows, bool count, bool chain) {
   const uint64_t bands = (uint64_t)(H / band_rows);
-  const uint64_t unit = std::max<uint64_t>(1, (uint64_t)L * H * W / (count ? 256 : 384));
-  if (L * bands > 512 || (!chain && 4 * unit > 8192)) return {1, 1};
-  return {(uint32_t)std::min<uint64_t>(64, 1024 / (L * bands)), (uint32_t)unit};
+  // four photons per thread of a 512-thread workgroup: on fewer, the loads of
+  // one step already cover the slice
+  const float slice = std::max(2048.0f, (float)L * H * W / (count ? 128 : 192));
+  if (L * bands > 512 || (!chain && 2 * slice > 8192)) return {1, 0.0f, 0.0f};
+  return {(uint32_t)std::min<uint64_t>(64, 1024 / (L * bands)), 1.0f / slice, (count ? 768.0f : 1152.0f) / ((float)L * H * W)};
 }
 
 template <int BPT, int NT, bool CUT, class LS>

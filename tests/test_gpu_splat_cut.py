@@ -50,13 +50,15 @@ def test_zeroing_pass(ctx, npg, L, H, W, launches):
     assert _launches(ctx, lambda: npg.splat_histograms(ctx, d, ww, o, H, W, energy=e, want_count=False)) == launches
 
 
-# photons about the first slices of 2048 (4096, 6144) and about n^2 units for n = 2
-# and 3; large maps with several bands; accumulated onto the first result
+# photons about two and three slices (of 2048, or L H W / 192 where that is more)
+# and about n^2 units (L H W / 1152) for n = 4 and 9; large maps with several bands;
+# accumulated onto the first result
 @pytest.mark.parametrize("L,H,W", [(60, 64, 64), (16, 128, 128), (3, 256, 256), (400, 16, 16)])
 @pytest.mark.parametrize("count", [False, True])
 def test_uneven_leaves_exact(ctx, npg, orc, L, H, W, count):
-    unit = max(1, L * H * W // (256 if count else 384))
-    edges = [0, 1, 4095, 4096, 6143, 6144, 4 * unit - 1, 4 * unit, 9 * unit - 1, 9 * unit, 200 * unit, 60000]
+    q = L * H * W // (768 if count else 1152)  # unit
+    two = 2 * max(2048, 6 * q)
+    edges = [0, 1, two - 1, two, two * 3 // 2 - 1, two * 3 // 2, 16 * q - 1, 16 * q, 81 * q - 1, 81 * q, 60000]
     counts = [min(edges[i], 200000) if i < len(edges) else 5 for i in range(L)]
     dirs, w, off = _photons(L + H, counts)
     rc, e_ref, c_ref = orc.splat(dirs, w, off, H, W)
