@@ -495,10 +495,12 @@ size_t grid_for(uint64_t n) {
 // tables that do not stay in an XCD's 4 MiB L2.  128x128 maps, lane by lane
 // against together: 220 thousand queries on 178 leaves 23.0 / 23.5 us, 400
 // thousand 38.0 / 35.2; 3 million on 15 leaves (1 MB) 138 / 147, on 178 209 /
-// 174, on 2851 323 / 263.  Rows of up to 64 bins take one or two rounds:
-// together is faster or the same from 80 thousand queries on (32x32: 16.4 /
-// 16.6, 220 thousand 18.6 / 17.5; MIS on 64x64: 17.4 / 17.2, 3 million 147 /
-// 144).
+// 174, on 2851 323 / 263.  Rows of up to 64 bins take one or two rounds, and
+// together is faster or the same for any number of queries (200 leaves, one call
+// and the wait for it): 32x32 maps 1 query 23.0 / 22.7, 1000 28.0 / 25.8, 80
+// thousand 27.9 / 27.0, 200 thousand 29.9 / 28.9; 64x64 23.2 / 22.7, 27.3 / 25.7,
+// 28.0 / 27.3, 31.7 / 30.4; MIS on 64x64 23.2 / 23.7, 27.6 / 26.5, 28.6 / 27.5,
+// 32.8 / 31.4.
 bool wide_search(const npg_tables &t, uint64_t n) {
   return (t.H <= 64 && t.W <= 64) || (n >= (1u << 18) && 4ull * t.L * t.H * (t.W + 1) > (4ull << 20));
 }
@@ -507,8 +509,8 @@ bool wide_search(const npg_tables &t, uint64_t n) {
 
 hipError_t launch_sample(const npg_tables &t, const uint32_t *leaf, const float *u, uint64_t n,
                          float *dir, float *pdf, uint32_t *bin, uint32_t *err, hipStream_t s) {
-  hipLaunchKernelGGL(wide_search(t, n) ? sample_kernel<true> : sample_kernel<false>, dim3(grid_for(n)), dim3(256), 0, s, t.pdf_dev, t.marg_dev, t.cond_dev,
-                     t.L, t.H, t.W, leaf, reinterpret_cast<const float2 *>(u), n, dir, pdf, bin, err);
+  hipLaunchKernelGGL(wide_search(t, n) ? sample_kernel<true> : sample_kernel<false>, dim3(grid_for(n)), dim3(256), 0,
+                     s, t.pdf_dev, t.marg_dev, t.cond_dev, t.L, t.H, t.W, leaf, reinterpret_cast<const float2 *>(u), n, dir, pdf, bin, err);
   return hipGetLastError();
 }
 
@@ -521,8 +523,8 @@ hipError_t launch_mis_alpha(const float *nu_b, const float *nu_g, const uint32_t
 hipError_t launch_sample_mis(const float2 *bnd, const npg_tables &t, const float *alpha, const uint32_t *leaf,
                              const float *normal, const float *u, uint64_t n, float *dir, float *pdf,
                              uint8_t *strat, uint32_t *err, hipStream_t s) {
-  hipLaunchKernelGGL(wide_search(t, n) ? sample_mis_kernel<true> : sample_mis_kernel<false>, dim3(grid_for(n)), dim3(256), 0, s, bnd, t.pdf_dev, t.marg_dev, t.cond_dev,
-                     t.L, t.H, t.W, alpha, leaf, normal, u, n, dir, pdf, strat, err);
+  hipLaunchKernelGGL(wide_search(t, n) ? sample_mis_kernel<true> : sample_mis_kernel<false>, dim3(grid_for(n)),
+                     dim3(256), 0, s, bnd, t.pdf_dev, t.marg_dev, t.cond_dev, t.L, t.H, t.W, alpha, leaf, normal, u, n, dir, pdf, strat, err);
   return hipGetLastError();
 }
 
