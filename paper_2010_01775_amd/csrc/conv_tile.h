@@ -37,7 +37,7 @@ struct TileArgs {
                                             // upsampling (s0) and the skip tensor (s1)
   int C0 = 0, C1 = 0;                       // their channels
   int H = 0, W = 0, Lc = 0;                 // output map, leaves in this launch
-  int Cin = 0, Cout = 0, nchunk = 0;
+  int Cout = 0, nchunk = 0;
   size_t lds_budget = 0;                    // LDS for chunks staged together; 0: one at a time
   int cstage = 1;                           // chunks staged per barrier (set by the launch)
   int TR = 0, TL = 1;                       // rows per leaf and leaves of a tile

@@ -600,7 +600,7 @@ __device__ __forceinline__ void select_wave(const SelArgs &a, uint32_t j, uint32
   if (split) {
     axis = longest_axis(a.lv.box + 6 * (size_t)j);
     const bool copy_n = a.nrm_s && !tested;
-    // keys of the split axis and their range (as in kd_select_kernel)
+    // keys of the split axis and their range (as in select_group)
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0;
     for (uint32_t i0 = 0; i0 < M; i0 += 4 * 64) {  // four keys in flight per lane
       uint32_t ph[4];

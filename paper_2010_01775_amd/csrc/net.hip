@@ -1801,7 +1801,7 @@ struct Runner {
       a.H = H;
       a.W = W;
       a.Lc = Lc;
-      a.Cin = a.Cout = a.C0 = 16;
+      a.Cout = a.C0 = 16;
       a.nchunk = 1;
       a.w = prec == NPG_FP8 ? (const void *)l1.pk8s : (const void *)l1.pk16s;
       a.bias = l1.b;
@@ -1823,44 +1823,44 @@ struct Runner {
       ctx->conv_flops[1] += 2.0 * Lc * H * W / (tr * tw) * (tr + 2.0) * (tw + 2.0) * 16.0 * 9.0;
       e = launch_lowp(a, ts, 16, TILE_FIRST);
     } else {
-    ConvArgs a{};
-    a.src = energy;
-    a.Cin = 16;
-    a.Cout = 16;
-    a.H = H;
-    a.W = W;
-    a.TW = t.TW;
-    a.TR = t.TR;
-    a.TL = t.TL;
-    a.Lc = Lc;
-    a.fPW = make_fastdiv((uint32_t)(t.TW + 2));
-    a.fPP = make_fastdiv((uint32_t)((t.TW + 2) * (t.TR + 2)));
-    a.fTW = make_fastdiv((uint32_t)t.TW);
-    a.fTPX = make_fastdiv((uint32_t)(t.TW * t.TR));
-    a.tiles_x = W / t.TW;
-    a.tiles_per_leaf = (H / t.TR) * a.tiles_x;
-    a.nchunk = 16 / KC32;
-    a.bias = l1.b;
-    a.head_w = nullptr;
-    a.wsc = l1.wsc8;
-    a.oinv = 1.0f / l1.a8;
-    a.asc = l1.a8;
-    a.w0 = l0.w;
-    a.b0 = l0.b;
-    a.oinv0 = 1.0f;
-    a.out = out;
-    if (pool_out && t.TR % 2 == 0 && t.TW % 2 == 0) {
-      a.pool_out = pool_out;
-      pooled = true;
-    }
-    const unsigned tiles = (unsigned)((Lc + t.TL - 1) / t.TL) * a.tiles_per_leaf;
-    // layer 1 on the matrix cores; layer 0 recomputed on the vector ALUs for
-    // every patch pixel (the tile and its one-pixel halo)
-    ctx->conv_flops[0] += 2.0 * Lc * H * W * 16.0 * 9.0 * 16.0;
-    ctx->conv_flops[1] += 2.0 * tiles * t.TL * (t.TR + 2.0) * (t.TW + 2.0) * 16.0 * 9.0;
-    a.wpk = l1.pk32;
-    a.wpk64 = l1.pk64;
-    e = launch_mfma<F32P>(a, t, tiles, s);
+      ConvArgs a{};
+      a.src = energy;
+      a.Cin = 16;
+      a.Cout = 16;
+      a.H = H;
+      a.W = W;
+      a.TW = t.TW;
+      a.TR = t.TR;
+      a.TL = t.TL;
+      a.Lc = Lc;
+      a.fPW = make_fastdiv((uint32_t)(t.TW + 2));
+      a.fPP = make_fastdiv((uint32_t)((t.TW + 2) * (t.TR + 2)));
+      a.fTW = make_fastdiv((uint32_t)t.TW);
+      a.fTPX = make_fastdiv((uint32_t)(t.TW * t.TR));
+      a.tiles_x = W / t.TW;
+      a.tiles_per_leaf = (H / t.TR) * a.tiles_x;
+      a.nchunk = 16 / KC32;
+      a.bias = l1.b;
+      a.head_w = nullptr;
+      a.wsc = l1.wsc8;
+      a.oinv = 1.0f / l1.a8;
+      a.asc = l1.a8;
+      a.w0 = l0.w;
+      a.b0 = l0.b;
+      a.oinv0 = 1.0f;
+      a.out = out;
+      if (pool_out && t.TR % 2 == 0 && t.TW % 2 == 0) {
+        a.pool_out = pool_out;
+        pooled = true;
+      }
+      const unsigned tiles = (unsigned)((Lc + t.TL - 1) / t.TL) * a.tiles_per_leaf;
+      // layer 1 on the matrix cores; layer 0 recomputed on the vector ALUs for
+      // every patch pixel (the tile and its one-pixel halo)
+      ctx->conv_flops[0] += 2.0 * Lc * H * W * 16.0 * 9.0 * 16.0;
+      ctx->conv_flops[1] += 2.0 * tiles * t.TL * (t.TR + 2.0) * (t.TW + 2.0) * 16.0 * 9.0;
+      a.wpk = l1.pk32;
+      a.wpk64 = l1.pk64;
+      e = launch_mfma<F32P>(a, t, tiles, s);
     }
     if (e != hipSuccess) return npg_fail(ctx, NPG_E_HIP, "fused first conv launch: %s", hipGetErrorString(e));
     if (ev) {
@@ -1927,7 +1927,6 @@ struct Runner {
       a.H = H;
       a.W = W;
       a.Lc = Lc;
-      a.Cin = y.cin;
       a.Cout = y.cout;
       a.nchunk = (y.cin + kc - 1) / kc;
       a.lds_budget = tile_lds(wgs);
