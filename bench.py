@@ -949,7 +949,8 @@ def run_path(args, workload: str, with_baseline: bool = True) -> dict:
     src_sha = sha_of(os.path.join(ROOT, "paper_2010_01775_amd", "csrc", "net.hip"))
     if os.path.exists(tfile) and not args.experts and not args.input5:
         t = json.load(open(tfile))
-        if t.get("source_sha") == src_sha:
+        tile_sha = sha_of(os.path.join(ROOT, "paper_2010_01775_amd", "csrc", "conv_tile.h"))  # the 8/16-bit layers
+        if t.get("source_sha") == src_sha and t.get("tile_sha") == tile_sha:
             traffic = t.get("bytes_per_launch")
 
     stage_roof = {}

@@ -2,11 +2,13 @@
 // tile geometry fixed at compile time.
 //
 // A workgroup (4 wavefronts) computes 64 * MW output pixels x 16 * NW output
-// channels.  What bounds these layers is not the matrix cores but the vector
-// instructions issued beside them (16 cycles of matrix work per product, four
-// per vector instruction) and, on the 16-channel full-resolution layers, HBM.
-// So everything that does not depend on the chunk is computed once per tile
-// or at compile time:
+// channels.  What bounds these layers is not the matrix cores (10 to 55 % busy in
+// BF16; 16 cycles of work per product) but, where little is multiplied per
+// pixel, the vector instructions beside them: on full-resolution maps with 16
+// channels the vector ALUs are 80 to 87 % busy in the tile that computes the first
+// layer and in the one with the head; the one behind an upsampling runs at 5.3
+// TB/s in BF16.  So everything that does not depend on the chunk is computed
+// once per tile or at compile time:
 //  - a thread's staging offsets (input patch and weights) are computed once;
 //    a chunk of KC input channels only moves the buffers' base addresses;
 //  - the nine taps are unrolled, and every LDS fragment read is one of three
@@ -19,8 +21,8 @@
 //    consecutive channels of pixel lr, and row swaps between the lanes of two
 //    channel blocks make that 16 bytes, whole pixels per instruction; the 2x2
 //    means of the next level are formed from the same registers.
-// BF16 network on 1501 leaves of 128x128: 3799 -> 2875 us, FP8 on 1024 of 64x64:
-// 544 -> 397 us, against the tiles with run-time geometry.
+// BF16 network on 1501 leaves of 128x128: 3770 -> 2865 us, FP8 on 1024 of 64x64:
+// 545 -> 398 us, against the tiles with run-time geometry.
 //
 // Every output sums its terms in the same order whatever the tile: chunks in
 // order, then taps in order (for 16-channel chunks pairs of taps, one product
