@@ -947,7 +947,7 @@ def run_path(args, workload: str, with_baseline: bool = True) -> dict:
     traffic = None
     tfile = os.path.join(ROOT, "profiles", f"traffic_{workload}_{args.precision}.json")
     src_sha = sha_of(os.path.join(ROOT, "paper_2010_01775_amd", "csrc", "net.hip"))
-    if os.path.exists(tfile) and not args.experts and not args.input5:
+    if os.path.exists(tfile) and not args.experts and not args.input5 and args.hierarchy == "octree":
         t = json.load(open(tfile))
         tile_sha = sha_of(os.path.join(ROOT, "paper_2010_01775_amd", "csrc", "conv_tile.h"))  # the 8/16-bit layers
         if t.get("source_sha") == src_sha and t.get("tile_sha") == tile_sha:

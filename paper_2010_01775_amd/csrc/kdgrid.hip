@@ -28,11 +28,12 @@
 // KD_AHEAD levels before the host knows whether the first of them has any.
 // Waiting for each level's count cost 60 us a level, as much as a level's work from
 // the fourth on.  20 million photons in 100^3 voxels, depth 8, with 2 million
-// locations: 3.98 -> 2.84 ms, together with the bitmaps (250 us of flags and
-// scans over the photons -> 60), wavefronts instead of workgroups for small
-// nodes in the partition (250 -> 100 us a level where 300 thousand nodes hold
-// the photons), 1024 threads for large ones, and photons copied into voxel
-// order by the first level (the others' selections 150 -> 90 us).
+// locations: 3.3 to 3.75 -> 2.3 to 2.65 ms by the photons, together with the
+// bitmaps (250 us of flags and scans over the photons -> 60), wavefronts instead
+// of workgroups for small nodes in the partition (250 -> 100 us a level where 300
+// thousand nodes hold the photons), 1024 threads for large ones, and photons
+// copied into voxel order by the first level (the others' selections 150 -> 90
+// us).
 // Point location: voxel id, then down the tree by the split comparisons.
 #include "npg_internal.h"
 
