@@ -501,16 +501,26 @@ size_t grid_for(uint64_t n) {
 // thousand 27.9 / 27.0, 200 thousand 29.9 / 28.9; 64x64 23.2 / 22.7, 27.3 / 25.7,
 // 28.0 / 27.3, 31.7 / 30.4; MIS on 64x64 23.2 / 23.7, 27.6 / 26.5, 28.6 / 27.5,
 // 32.8 / 31.4.
-bool wide_search(const npg_tables &t, uint64_t n) {
-  return (t.H <= 64 && t.W <= 64) || (n >= (1u << 18) && 4ull * t.L * t.H * (t.W + 1) > (4ull << 20));
+// A mixture sample searches only half the time and waits for memory less, so there
+// the tables have to be further past the L2, and for many queries further still.
+// Lane by lane against together, 300 and 600 thousand queries: one leaf of
+// 1024x1024 (4 MiB) 14.4 / 14.8 and 21.7 / 24.1 us, 5 of 512x512 (5 MiB) 14.8 / 14.3
+// and 23.2 / 23.4, 100 of 128x128 (6 MiB) 15.2 / 14.3 and 25.0 / 24.1; 1 and 10
+// million: 1024x1024 30.9 / 34.8 and 262 / 299, 8 of 512x512 35.3 / 36.9 and 289 /
+// 303, 200 of 128x128 (13 MiB) 37.8 / 38.8 and 314 / 316, 8 of 1024x1024 (32 MiB)
+// 39.7 / 42.0 and 333 / 331, 4000 of 128x128 47.5 / 47.7 and 424 / 409.
+bool wide_search(const npg_tables &t, uint64_t n, bool mis) {
+  const uint64_t fits = (!mis ? 4u : n < 900000 ? 6u : 16u) << 20;
+  return (t.H <= 64 && t.W <= 64) || (n >= (1u << 18) && 4ull * t.L * t.H * (t.W + 1) > fits);
 }
 
 }  // namespace
 
 hipError_t launch_sample(const npg_tables &t, const uint32_t *leaf, const float *u, uint64_t n,
                          float *dir, float *pdf, uint32_t *bin, uint32_t *err, hipStream_t s) {
-  hipLaunchKernelGGL(wide_search(t, n) ? sample_kernel<true> : sample_kernel<false>, dim3(grid_for(n)), dim3(256), 0,
-                     s, t.pdf_dev, t.marg_dev, t.cond_dev, t.L, t.H, t.W, leaf, reinterpret_cast<const float2 *>(u), n, dir, pdf, bin, err);
+  hipLaunchKernelGGL(wide_search(t, n, false) ? sample_kernel<true> : sample_kernel<false>, dim3(grid_for(n)),
+                     dim3(256), 0, s, t.pdf_dev, t.marg_dev, t.cond_dev, t.L, t.H, t.W, leaf,
+                     reinterpret_cast<const float2 *>(u), n, dir, pdf, bin, err);
   return hipGetLastError();
 }
 
@@ -523,8 +533,9 @@ hipError_t launch_mis_alpha(const float *nu_b, const float *nu_g, const uint32_t
 hipError_t launch_sample_mis(const float2 *bnd, const npg_tables &t, const float *alpha, const uint32_t *leaf,
                              const float *normal, const float *u, uint64_t n, float *dir, float *pdf,
                              uint8_t *strat, uint32_t *err, hipStream_t s) {
-  hipLaunchKernelGGL(wide_search(t, n) ? sample_mis_kernel<true> : sample_mis_kernel<false>, dim3(grid_for(n)),
-                     dim3(256), 0, s, bnd, t.pdf_dev, t.marg_dev, t.cond_dev, t.L, t.H, t.W, alpha, leaf, normal, u, n, dir, pdf, strat, err);
+  hipLaunchKernelGGL(wide_search(t, n, true) ? sample_mis_kernel<true> : sample_mis_kernel<false>, dim3(grid_for(n)),
+                     dim3(256), 0, s, bnd, t.pdf_dev, t.marg_dev, t.cond_dev, t.L, t.H, t.W, alpha, leaf, normal, u, n,
+                     dir, pdf, strat, err);
   return hipGetLastError();
 }
 
